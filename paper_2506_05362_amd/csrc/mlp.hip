@@ -3,11 +3,11 @@
 // include/pd_mlp.h.
 //
 // Every layer product is one kernel k_gemm: a 256-thread workgroup computes a
-// 64 x 64 tile of C = A B with gfx950's v_mfma_f32_16x16x32_bf16 (each
-// wavefront owns a 32 x 32 quarter as 2 x 2 matrix-core blocks); A and B are
-// read from FP32 arrays through arbitrary strides (so the transposed operands
-// of the backward pass need no copies), rounded to BF16 and staged in LDS 32
-// columns of K at a time.
+// 64 x 64 or 32 x 32 tile of C = A B with gfx950's v_mfma_f32_16x16x32_bf16
+// (each wavefront owns a quarter of the tile); A and B are read from FP32 arrays
+// in their own layout (so the transposed operands of the backward pass need no
+// copies), rounded to BF16 and staged in LDS 64 or 128 columns of K at a time.
+// The weight and bias gradients of all layers are one kernel, k_wgrad.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "pd_mlp.h"
@@ -26,12 +27,11 @@ namespace {
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int kTile = 64;
-constexpr int kK = 32;
-constexpr int kKRow = kK + 8;  // LDS row of a staged tile (bf16): 16-byte aligned, banks staggered
+typedef float v8f __attribute__((ext_vector_type(8)));
 
 // C += A B on the matrix cores, 16 x 16 x 32 in BF16 with FP32 accumulation.
 // Lane l holds 8 consecutive k of row l % 16 of A (group l / 16) and the same
@@ -47,6 +47,14 @@ __device__ __forceinline__ short to_bf16(float x) {
   if ((u & 0x7fffffffu) > 0x7f800000u) return (short)((u >> 16) | 0x40u);
   u += 0x7fffu + ((u >> 16) & 1u);
   return (short)(u >> 16);
+}
+
+__device__ __forceinline__ v8s to_bf16x8(const v8f& x) {
+  return __builtin_bit_cast(v8s, __builtin_convertvector(x, v8bf));
+}
+
+__device__ __forceinline__ v4s to_bf16x4(const v4f& x) {
+  return __builtin_bit_cast(v4s, __builtin_convertvector(x, v4bf));
 }
 
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
@@ -67,64 +75,131 @@ struct Gemm {
   const float* Zin;    // pre-activation for GELU' (ldc)
 };
 
-enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_GRAD = 3 };
+enum { EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_GRAD = 3 };
 
-// Eight consecutive k of one row (or column) of an operand, rounded to BF16:
-// X(k) = p[k * sk] for k0 <= k < k0 + 8, zero past K or where ok is false.
-// A contiguous, 16-byte aligned run inside K is read as two float4.
-__device__ __forceinline__ v8s load8_bf16(const float* p, int64_t sk, int64_t k0, int64_t K, bool ok) {
-  v8s r;
-  if (ok && sk == 1 && k0 + 8 <= K && ((reinterpret_cast<uintptr_t>(p + k0) & 15u) == 0)) {
-    const float4 x = *reinterpret_cast<const float4*>(p + k0);
-    const float4 y = *reinterpret_cast<const float4*>(p + k0 + 4);
-    r = v8s{to_bf16(x.x), to_bf16(x.y), to_bf16(x.z), to_bf16(x.w), to_bf16(y.x), to_bf16(y.y), to_bf16(y.z),
-            to_bf16(y.w)};
-  } else {
+// How an operand's 8 consecutive k are read: one by one with the rows side by
+// side in memory (any stride), one by one along k, or as two float4 along k
+// (K a multiple of 8, rows 16-byte aligned).
+enum { ROWS = 0, ALONG_K = 1, ALONG_K4 = 2 };
+
+// The k0..k0+KC-1 columns of T rows of an operand (row i at p + i * srow), 8 k
+// per thread and group.  Where k is the contiguous direction the KC / 8 threads
+// of a row sit side by side; where the rows are, the threads of one group of
+// 8 k do, so that each of its 8 loads is one coalesced run.  Every load is
+// issued without a branch (rows and k past the end read the last one, and are
+// zeroed on the way to LDS): behind a branch each would wait for the one before.
+template <int T, int KC, int MODE>
+struct Stage {
+  static constexpr int kGroups = T * KC / 8 / 256;
+  v8f x[kGroups];
+  const float* q[kGroups];
+  __device__ __forceinline__ static void place(int g, int& row, int& kk) {
+    const int id = threadIdx.x + g * 256;
+    row = MODE == ROWS ? id % T : id / (KC / 8);
+    kk = (MODE == ROWS ? id / T : id % (KC / 8)) * 8;
+  }
+  __device__ __forceinline__ void init(const float* p, int64_t srow, int64_t r0, int64_t R) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t k = k0 + e;
-      r[e] = to_bf16((ok && k < K) ? p[k * sk] : 0.0f);
+    for (int g = 0; g < kGroups; ++g) {
+      int row, kk;
+      place(g, row, kk);
+      q[g] = p + (r0 + row < R ? r0 + row : R - 1) * srow;
     }
   }
-  return r;
+  __device__ __forceinline__ void load(int64_t sk, int k0, int K) {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      int row, kk;
+      place(g, row, kk);
+      if (MODE == ALONG_K4) {
+        const int k = k0 + kk < K ? k0 + kk : K - 8;
+        const v4f a = *reinterpret_cast<const v4f*>(q[g] + k), b = *reinterpret_cast<const v4f*>(q[g] + k + 4);
+        x[g] = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int k = k0 + kk + e < K ? k0 + kk + e : K - 1;
+          x[g][e] = q[g][MODE == ROWS ? k * sk : (int64_t)k];
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void store(short (*s)[KC + 8], int k0, int K) const {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      int row, kk;
+      place(g, row, kk);
+      v8s v = to_bf16x8(x[g]);
+      if (k0 + KC > K) {  // the last chunk's missing k add exact zeros
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (k0 + kk + e >= K) v[e] = 0;
+      }
+      *reinterpret_cast<v8s*>(&s[row][kk]) = v;
+    }
+  }
+};
+
+// One KC-deep chunk from LDS: wavefront w owns the quarter (w / 2, w % 2) of the
+// T x T tile as NB x NB matrix-core blocks.  Every element adds its k in
+// steps of 32, ascending, into one accumulator, whatever T and KC are.
+template <int T, int KC, int NB>
+__device__ __forceinline__ void gemm_chunk(const short (*As)[KC + 8], const short (*Bs)[KC + 8], int wm, int wn,
+                                           int lane, v4f (&acc)[NB][NB]) {
+#pragma unroll
+  for (int k = 0; k < KC; k += 32) {
+    v8s a[NB], b[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) a[i] = *reinterpret_cast<const v8s*>(&As[wm + i * 16 + (lane & 15)][k + 8 * (lane >> 4)]);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] = *reinterpret_cast<const v8s*>(&Bs[wn + j * 16 + (lane & 15)][k + 8 * (lane >> 4)]);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] = mfma_16x16x32(a[i], b[j], acc[i][j]);
+  }
 }
 
-template <int EPI>
+// KC k at a time; the next chunk's loads travel while this one is multiplied.
+// Bound by the latency of its one or few rounds of loads at small batches (512 x
+// 256 x 256: 5.4 us, 25 us with 32 k a round and one workgroup on every eighth
+// CU), by its FP32 operands and the exact-erf GELU at large ones (16384 x 256 x
+// 256: 19.5 us for 50 MB, 33 us before).
+template <int EPI, int T, int KC, int MA, int MB>
 __global__ __launch_bounds__(256) void k_gemm(Gemm g) {
-  __shared__ __align__(16) short As[kTile][kKRow];  // As[m][k]
-  __shared__ __align__(16) short Bs[kTile][kKRow];  // Bs[n][k] (B transposed)
+  __shared__ __align__(16) short As[T][KC + 8];  // As[m][k]
+  __shared__ __align__(16) short Bs[T][KC + 8];  // Bs[n][k] (B transposed)
+  constexpr int NB = T / 32;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t m0 = (int64_t)blockIdx.y * kTile, n0 = (int64_t)blockIdx.x * kTile;
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-  v4f acc[2][2];
+  const int64_t m0 = (int64_t)blockIdx.y * T, n0 = (int64_t)blockIdx.x * T;
+  const int wm = (wv >> 1) * (T / 2), wn = (wv & 1) * (T / 2);
+  v4f acc[NB][NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  const int lr = tid >> 2, lk = (tid & 3) * 8;  // staging: row / column of the tile, 8 k each
-  for (int64_t k0 = 0; k0 < g.K; k0 += kK) {
-    {
-      // one 16-byte LDS store per operand and thread
-      const int64_t m = m0 + lr, n = n0 + lr;
-      *reinterpret_cast<v8s*>(&As[lr][lk]) = load8_bf16(g.A + (m < g.M ? m * g.sam : 0), g.sak, k0 + lk, g.K, m < g.M);
-      *reinterpret_cast<v8s*>(&Bs[lr][lk]) = load8_bf16(g.B + (n < g.N ? n * g.sbn : 0), g.sbk, k0 + lk, g.K, n < g.N);
-    }
+    for (int j = 0; j < NB; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  const int K = (int)g.K;
+  Stage<T, KC, MA> sa;
+  Stage<T, KC, MB> sb;
+  sa.init(g.A, g.sam, m0, g.M);
+  sb.init(g.B, g.sbn, n0, g.N);
+  sa.load(g.sak, 0, K);
+  sb.load(g.sbk, 0, K);
+  for (int k0 = 0; k0 < K; k0 += KC) {
+    sa.store(As, k0, K);
+    sb.store(Bs, k0, K);
     __syncthreads();
-    v8s a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const v8s*>(&As[wm + i * 16 + (lane & 15)][8 * (lane >> 4)]);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const v8s*>(&Bs[wn + j * 16 + (lane & 15)][8 * (lane >> 4)]);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = mfma_16x16x32(a[i], b[j], acc[i][j]);
+    if (k0 + KC < K) {
+      sa.load(g.sak, k0 + KC, K);
+      sb.load(g.sbk, k0 + KC, K);
+    }
+    gemm_chunk<T, KC, NB>(As, Bs, wm, wn, lane, acc);
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int64_t m = m0 + wm + i * 16 + 4 * (lane >> 4) + e;
@@ -132,9 +207,7 @@ __global__ __launch_bounds__(256) void k_gemm(Gemm g) {
         if (m >= g.M || n >= g.N) continue;
         const float v = acc[i][j][e];
         const int64_t o = m * g.ldc + n;
-        if (EPI == EPI_STORE) {
-          g.C[o] = v;
-        } else if (EPI == EPI_BIAS) {
+        if (EPI == EPI_BIAS) {
           g.C[o] = v + g.bias[n];
         } else if (EPI == EPI_BIAS_GELU) {
           const float z = v + g.bias[n];
@@ -146,17 +219,188 @@ __global__ __launch_bounds__(256) void k_gemm(Gemm g) {
       }
 }
 
-// residual, loss partial sums and dY = 2 (Y_hat - Y) / (B * d)
-__global__ __launch_bounds__(256) void k_loss(const float* yh, const float* y, float* dy, int64_t n,
-                                               float scale, double* partial) {
+// ---------------------------------------------------------------------------
+// Weight and bias gradients of every layer in one launch: dW_l = A_{l-1}^T dZ_l
+// and db_l = column sums of dZ_l.  Each element is one sum over the batch, in
+// row order: a matrix-core accumulator taking 32 rows at a time for dW, plain
+// FP32 additions of the unrounded dZ for db.  What bounds it is the latency of
+// walking the batch, so the outputs are cut small (32 x 32 tiles of dW, 64
+// columns of db, in workgroups of their own since an addition chain is slower
+// than the matrix cores) and each workgroup keeps kWD chunks of kWK rows in
+// flight in registers.  All four layers of 6-256-256-256-7: 8.8 us at 512 rows,
+// 162 us at 16384 (four dW and four column-sum launches one after the other: 650
+// us and 22.9 ms).  Splitting the batch over workgroups as well took 46 us at
+// 16384 rows, but sums in another order: the difference of 4e-7 in the gradient
+// passes through Adam's first steps, which for gradients near eps is 1e-3 of a
+// weight.
+// ---------------------------------------------------------------------------
+
+constexpr int kWT = 32, kWK = 128, kWD = 4;
+constexpr int kBT = 64, kBD = 4;   // columns of a bias workgroup, its chunks in flight
+constexpr int kGroupLayers = 8;    // layers per launch
+
+struct WGrad {
+  const float* A;   // layer input, din of lda columns
+  const float* dZ;  // dl of ldz columns
+  int32_t din, lda, dl, ldz;
+  int32_t tiles_n, tiles_w;  // tiles of dW across, and in all; bias workgroups follow
+  float *dW, *db;
+};
+struct WGradGroup {
+  WGrad l[kGroupLayers];
+  int32_t block0[kGroupLayers + 1];  // workgroups before layer l
+  int32_t layers;
+  int64_t batch;
+};
+
+// One chunk of T columns of a row-major [batch][ld] array in registers: blocks of
+// 4 rows x 4 columns, T / 4 threads side by side (ld a multiple of 4, 16-byte
+// aligned).  Loads are issued without a branch, as above; columns past ld feed
+// only outputs that are not stored, rows past the batch are zeroed on the way to
+// LDS.
+template <int T>
+struct Rows {
+  static constexpr int kBlocks = T * kWK / 16 / 256;
+  v4f x[kBlocks][4];
+  __device__ __forceinline__ static int col() { return threadIdx.x % (T / 4) * 4; }
+  __device__ __forceinline__ static int row(int g) { return (threadIdx.x / (T / 4) + g * (256 / (T / 4))) * 4; }
+  __device__ __forceinline__ void load(const float* p, int ld, int c0, int64_t b0, int64_t batch) {
+    const int c = c0 + col() < ld ? c0 + col() : ld - 4;
+#pragma unroll
+    for (int g = 0; g < kBlocks; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t r = b0 + row(g) + e;
+        x[g][e] = *reinterpret_cast<const v4f*>(p + (r < batch ? r : batch - 1) * ld + c);
+      }
+  }
+  __device__ __forceinline__ void mask(int64_t b0, int64_t batch) {
+#pragma unroll
+    for (int g = 0; g < kBlocks; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (b0 + row(g) + e >= batch) x[g][e] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  // column k of block g: its four rows
+  __device__ __forceinline__ v4f column(int g, int k) const { return v4f{x[g][0][k], x[g][1][k], x[g][2][k], x[g][3][k]}; }
+};
+
+__device__ __forceinline__ void wgrad_bias(const WGrad& L, int n0, int64_t batch, char* lds) {
+  float(*s)[kBT][kWK + 4] = reinterpret_cast<float(*)[kBT][kWK + 4]>(lds);  // s[buffer][n][k]
+  using R = Rows<kBT>;
+  R x[kBD];
+#pragma unroll
+  for (int d = 0; d < kBD; ++d) x[d].load(L.dZ, L.ldz, n0, d * kWK, batch);
+  float sum = 0.0f;
+  // rounds of kBD chunks, the last one masked (a branch in the others would have
+  // every load waited for): rows past the batch hold zeros, which change no sum
+  auto round = [&](int64_t c0, auto masked) {
+#pragma unroll
+    for (int d = 0; d < kBD; ++d) {
+      const int64_t b0 = c0 + d * kWK;
+      const int buf = d & 1;
+      if (masked) x[d].mask(b0, batch);
+#pragma unroll
+      for (int g = 0; g < R::kBlocks; ++g)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) *reinterpret_cast<v4f*>(&s[buf][R::col() + k][R::row(g)]) = x[d].column(g, k);
+      __syncthreads();  // the other buffer was read before this barrier's arrival
+      x[d].load(L.dZ, L.ldz, n0, b0 + kBD * kWK, batch);
+      if (threadIdx.x < kBT) {
+#pragma unroll
+        for (int r = 0; r < kWK; r += 4) {
+          const v4f v = *reinterpret_cast<const v4f*>(&s[buf][threadIdx.x][r]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum += v[e];
+        }
+      }
+    }
+  };
+  int64_t c0 = 0;
+  for (; c0 + kBD * kWK <= batch; c0 += kBD * kWK) round(c0, std::false_type{});
+  if (c0 < batch) round(c0, std::true_type{});
+  if (threadIdx.x < kBT && n0 + (int)threadIdx.x < L.dl) L.db[n0 + threadIdx.x] = sum;
+}
+
+__device__ __forceinline__ void wgrad_tile(const WGrad& L, int m0, int n0, int64_t batch, char* lds) {
+  short(*As)[kWT][kWK + 8] = reinterpret_cast<short(*)[kWT][kWK + 8]>(lds);  // As[buffer][m][k]
+  short(*Bs)[kWT][kWK + 8] = As + 2;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int wm = (wv >> 1) * (kWT / 2), wn = (wv & 1) * (kWT / 2);
+  v4f acc[1][1] = {{v4f{0.f, 0.f, 0.f, 0.f}}};
+  using R = Rows<kWT>;
+  R a[kWD], b[kWD];
+#pragma unroll
+  for (int d = 0; d < kWD; ++d) {
+    a[d].load(L.A, L.lda, m0, d * kWK, batch);
+    b[d].load(L.dZ, L.ldz, n0, d * kWK, batch);
+  }
+  auto round = [&](int64_t c0, auto masked) {
+#pragma unroll
+    for (int d = 0; d < kWD; ++d) {
+      const int64_t b0 = c0 + d * kWK;
+      const int buf = d & 1;
+      if (masked) {
+        a[d].mask(b0, batch);
+        b[d].mask(b0, batch);
+      }
+#pragma unroll
+      for (int g = 0; g < R::kBlocks; ++g)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          *reinterpret_cast<v4s*>(&As[buf][R::col() + k][R::row(g)]) = to_bf16x4(a[d].column(g, k));
+          *reinterpret_cast<v4s*>(&Bs[buf][R::col() + k][R::row(g)]) = to_bf16x4(b[d].column(g, k));
+        }
+      __syncthreads();  // the other buffer was read before this barrier's arrival
+      a[d].load(L.A, L.lda, m0, b0 + kWD * kWK, batch);
+      b[d].load(L.dZ, L.ldz, n0, b0 + kWD * kWK, batch);
+      gemm_chunk<kWT, kWK, 1>(As[buf], Bs[buf], wm, wn, lane, acc);
+    }
+  };
+  int64_t c0 = 0;
+  for (; c0 + kWD * kWK <= batch; c0 += kWD * kWK) round(c0, std::false_type{});
+  if (c0 < batch) round(c0, std::true_type{});
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int m = m0 + wm + 4 * (lane >> 4) + e, n = n0 + wn + (lane & 15);
+    if (m < L.din && n < L.dl) L.dW[m * L.dl + n] = acc[0][0][e];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_wgrad(WGradGroup G) {
+  constexpr int kTileBytes = 2 * 2 * kWT * (kWK + 8) * (int)sizeof(short), kBiasBytes = 2 * kBT * (kWK + 4) * (int)sizeof(float);
+  __shared__ __align__(16) char smem[kTileBytes > kBiasBytes ? kTileBytes : kBiasBytes];
+  int li = 0;
+  while (li + 1 < G.layers && (int)blockIdx.x >= G.block0[li + 1]) ++li;
+  const WGrad L = G.l[li];
+  const int t = (int)blockIdx.x - G.block0[li];
+  if (t >= L.tiles_w) wgrad_bias(L, (t - L.tiles_w) * kBT, G.batch, smem);
+  else wgrad_tile(L, t / L.tiles_n * kWT, t % L.tiles_n * kWT, G.batch, smem);
+}
+
+// residual, loss partial sums and dY = 2 (Y_hat - Y) / (B * d) in rows of ldd
+// (the columns past d zero); with xp, also the input copied to rows of ldx: what
+// k_wgrad reads four columns at a time
+__global__ __launch_bounds__(256) void k_loss(const float* yh, const float* y, float* dy, int64_t rows, int d, int ldd,
+                                               float scale, double* partial, const float* x, int dx, float* xp,
+                                               int ldx) {
   __shared__ double red[256];
   const int tid = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * 256 + tid, step = (int64_t)gridDim.x * 256;
   double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < n; i += (int64_t)gridDim.x * 256) {
-    const float r = yh[i] - y[i];
+  for (int64_t i = i0; i < rows * ldd; i += step) {
+    const int64_t m = i / ldd;
+    const int n = (int)(i % ldd);
+    const float r = n < d ? yh[m * d + n] - y[m * d + n] : 0.0f;
     dy[i] = scale * r;
     s += (double)r * (double)r;
   }
+  if (xp)
+    for (int64_t i = i0; i < rows * ldx; i += step) {
+      const int64_t m = i / ldx;
+      const int n = (int)(i % ldx);
+      xp[i] = n < dx ? x[m * dx + n] : 0.0f;
+    }
   red[tid] = s;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
@@ -164,15 +408,6 @@ __global__ __launch_bounds__(256) void k_loss(const float* yh, const float* y, f
     __syncthreads();
   }
   if (tid == 0) partial[blockIdx.x] = red[0];
-}
-
-// db[n] = sum_m dZ[m][n]
-__global__ void k_colsum(const float* dz, int64_t M, int64_t N, float* db) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  float s = 0.0f;
-  for (int64_t m = 0; m < M; ++m) s += dz[m * N + n];
-  db[n] = s;
 }
 
 // Adam with decoupled weight decay: p -= lr (m_hat / (sqrt(v_hat) + eps) + wd p)
@@ -391,8 +626,9 @@ struct pdm_net {
   int own_stream = 0;
   std::string err;
   float *params = nullptr, *grad = nullptr, *m = nullptr, *v = nullptr;
-  std::vector<float*> Z, Aout, dZ;  // per layer, [max_batch][dims[l+1]]
+  std::vector<float*> Z, Aout, dZ;  // per layer, [max_batch][row4(dims[l+1])]
   float* yhat = nullptr;            // [max_batch][d_out]
+  float* xrows = nullptr;           // the training input with rows padded to 4 columns
   double* partial = nullptr;
   int nloss_blocks = 0;
   std::vector<int64_t> woff, boff;  // offsets of W_l, b_l in the parameter vector
@@ -444,15 +680,40 @@ pd_status alloc(pdm_net* n, T** p, int64_t count) {
     if (s_ != PD_OK) return s_;       \
   } while (0)
 
+// 64 x 64 tiles where they give every CU a workgroup, else 32 x 32 with chunks
+// of 128 k (a quarter of the work per workgroup, half the trips to memory): at
+// 512 x 256 x 256 the small tiles take 5.4 us
+template <int EPI, int MA, int MB>
+void gemm_modes(const Gemm& g, hipStream_t s) {
+  auto grid = [&](int t) { return dim3((unsigned)((g.N + t - 1) / t), (unsigned)((g.M + t - 1) / t)); };
+  const dim3 g64 = grid(64);
+  if ((int64_t)g64.x * g64.y >= 256) hipLaunchKernelGGL((k_gemm<EPI, 64, 64, MA, MB>), g64, dim3(256), 0, s, g);
+  else hipLaunchKernelGGL((k_gemm<EPI, 32, 128, MA, MB>), grid(32), dim3(256), 0, s, g);
+}
+
 template <int EPI>
 hipError_t gemm(const Gemm& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  dim3 grid((unsigned)((g.N + kTile - 1) / kTile), (unsigned)((g.M + kTile - 1) / kTile));
-  hipLaunchKernelGGL(k_gemm<EPI>, grid, dim3(256), 0, s, g);
+  const auto vec = [&](const float* p, int64_t srow) {
+    return g.K % 8 == 0 && srow % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15u) == 0;
+  };
+  // A is an activation or dZ, contiguous along k; so is W^T in the backward
+  // product, while the forward product's W is contiguous along its columns
+  if (EPI == EPI_GELU_GRAD) {
+    if (vec(g.A, g.sam) && vec(g.B, g.sbn)) gemm_modes<EPI, ALONG_K4, ALONG_K4>(g, s);
+    else gemm_modes<EPI, ALONG_K, ALONG_K>(g, s);
+  } else {
+    if (vec(g.A, g.sam)) gemm_modes<EPI, ALONG_K4, ROWS>(g, s);
+    else gemm_modes<EPI, ALONG_K, ROWS>(g, s);
+  }
   return hipGetLastError();
 }
 
 int n_layers(const pdm_net* n) { return (int)n->dims.size() - 1; }
+
+// row length of the network's own activation buffers: what k_wgrad can read four
+// columns at a time (the padding is never read into a result)
+int row4(int64_t w) { return (int)((w + 3) & ~int64_t(3)); }
 
 // forward of `batch` rows (<= max_batch) from x into y (device pointers)
 pd_status forward_chunk(pdm_net* n, const float* x, int64_t batch, float* y, bool keep_z) {
@@ -462,7 +723,7 @@ pd_status forward_chunk(pdm_net* n, const float* x, int64_t batch, float* y, boo
     const int64_t din = n->dims[l], dout = n->dims[l + 1];
     Gemm g{};
     g.A = A;
-    g.sam = din;
+    g.sam = l == 0 ? din : row4(din);
     g.sak = 1;
     g.B = n->params + n->woff[l];
     g.sbk = dout;
@@ -471,7 +732,7 @@ pd_status forward_chunk(pdm_net* n, const float* x, int64_t batch, float* y, boo
     g.N = dout;
     g.K = din;
     g.bias = n->params + n->boff[l];
-    g.ldc = dout;
+    g.ldc = l < L - 1 ? row4(dout) : dout;
     if (l < L - 1) {
       g.C = n->Aout[l];
       g.Zout = keep_z ? n->Z[l] : nullptr;
@@ -491,46 +752,51 @@ pd_status loss_and_grad(pdm_net* n, const float* x, const float* y, int64_t batc
   const int64_t dout = n->dims[L];
   TRY(forward_chunk(n, x, batch, n->yhat, true));
   const int64_t cnt = batch * dout;
-  hipLaunchKernelGGL(k_loss, dim3(n->nloss_blocks), dim3(256), 0, n->stream, n->yhat, y, n->dZ[L - 1],
-                     cnt, 2.0f / (float)cnt, n->partial);
+  const bool copy_x = n->dims[0] % 4 != 0 || (reinterpret_cast<uintptr_t>(x) & 15u) != 0;
+  hipLaunchKernelGGL(k_loss, dim3(n->nloss_blocks), dim3(256), 0, n->stream, n->yhat, y, n->dZ[L - 1], batch, (int)dout,
+                     row4(dout), 2.0f / (float)cnt, n->partial, x, n->dims[0], copy_x ? n->xrows : nullptr,
+                     row4(n->dims[0]));
   HIPCHK(n, hipGetLastError());
-  for (int l = L - 1; l >= 0; --l) {
+  for (int l = L - 1; l > 0; --l) {
     const int64_t din = n->dims[l], dl = n->dims[l + 1];
-    const float* Ain = l == 0 ? x : n->Aout[l - 1];
-    // dW_l = A_in^T dZ_l
-    Gemm gw{};
-    gw.A = Ain;
-    gw.sam = 1;
-    gw.sak = din;
-    gw.B = n->dZ[l];
-    gw.sbk = dl;
-    gw.sbn = 1;
-    gw.M = din;
-    gw.N = dl;
-    gw.K = batch;
-    gw.C = n->grad + n->woff[l];
-    gw.ldc = dl;
-    HIPCHK(n, gemm<EPI_STORE>(gw, n->stream));
-    hipLaunchKernelGGL(k_colsum, dim3((unsigned)((dl + 255) / 256)), dim3(256), 0, n->stream, n->dZ[l],
-                       batch, dl, n->grad + n->boff[l]);
-    HIPCHK(n, hipGetLastError());
-    if (l > 0) {
-      // dZ_{l-1} = (dZ_l W_l^T) * GELU'(Z_{l-1})
-      Gemm gx{};
-      gx.A = n->dZ[l];
-      gx.sam = dl;
-      gx.sak = 1;
-      gx.B = n->params + n->woff[l];
-      gx.sbk = 1;
-      gx.sbn = dl;
-      gx.M = batch;
-      gx.N = din;
-      gx.K = dl;
-      gx.C = n->dZ[l - 1];
-      gx.ldc = din;
-      gx.Zin = n->Z[l - 1];
-      HIPCHK(n, gemm<EPI_GELU_GRAD>(gx, n->stream));
+    // dZ_{l-1} = (dZ_l W_l^T) * GELU'(Z_{l-1})
+    Gemm gx{};
+    gx.A = n->dZ[l];
+    gx.sam = row4(dl);
+    gx.sak = 1;
+    gx.B = n->params + n->woff[l];
+    gx.sbk = 1;
+    gx.sbn = dl;
+    gx.M = batch;
+    gx.N = din;
+    gx.K = dl;
+    gx.C = n->dZ[l - 1];
+    gx.ldc = row4(din);
+    gx.Zin = n->Z[l - 1];
+    HIPCHK(n, gemm<EPI_GELU_GRAD>(gx, n->stream));
+  }
+  WGradGroup G{};
+  G.batch = batch;
+  for (int l0 = 0; l0 < L; l0 += kGroupLayers) {
+    G.layers = std::min(kGroupLayers, L - l0);
+    G.block0[0] = 0;
+    for (int k = 0; k < G.layers; ++k) {
+      const int l = l0 + k;
+      WGrad& w = G.l[k];
+      w.A = l > 0 ? n->Aout[l - 1] : copy_x ? n->xrows : x;
+      w.dZ = n->dZ[l];
+      w.din = n->dims[l];
+      w.lda = row4(w.din);
+      w.dl = n->dims[l + 1];
+      w.ldz = row4(w.dl);
+      w.dW = n->grad + n->woff[l];
+      w.db = n->grad + n->boff[l];
+      w.tiles_n = (w.dl + kWT - 1) / kWT;
+      w.tiles_w = ((w.din + kWT - 1) / kWT) * w.tiles_n;
+      G.block0[k + 1] = G.block0[k] + w.tiles_w + (w.dl + kBT - 1) / kBT;
     }
+    hipLaunchKernelGGL(k_wgrad, dim3((unsigned)G.block0[G.layers]), dim3(256), 0, n->stream, G);
+    HIPCHK(n, hipGetLastError());
   }
   if (loss) {
     std::vector<double> part((size_t)n->nloss_blocks);
@@ -587,11 +853,12 @@ pd_status pdm_create(pdm_net** out, const int32_t* dims, int32_t n_dims, int64_t
   n->Aout.resize(L);
   n->dZ.resize(L);
   for (int l = 0; l < L; ++l) {
-    TRY(alloc(n, &n->Z[l], max_batch * dims[l + 1]));
-    TRY(alloc(n, &n->Aout[l], max_batch * dims[l + 1]));
-    TRY(alloc(n, &n->dZ[l], max_batch * dims[l + 1]));
+    TRY(alloc(n, &n->Z[l], max_batch * row4(dims[l + 1])));
+    TRY(alloc(n, &n->Aout[l], max_batch * row4(dims[l + 1])));
+    TRY(alloc(n, &n->dZ[l], max_batch * row4(dims[l + 1])));
   }
   TRY(alloc(n, &n->yhat, max_batch * dims[L]));
+  TRY(alloc(n, &n->xrows, max_batch * row4(dims[0])));
   if (n_dims == 5 && dims[1] == kH && dims[2] == kH && dims[3] == kH && dims[0] <= 16 && dims[4] <= 16) {
     int dev = 0, lds = 0;
     const size_t need_a = dims[0] <= 8 ? lds_a<8>() : lds_a<16>();
