@@ -1554,7 +1554,9 @@ pd_status pd_get(pd_ctx* c, pd_field f, void* dst, int64_t dst_bytes, int32_t ds
   if (dst_bytes < need) return fail(c, PD_ERR_INVALID, "dst too small: field needs %lld bytes", (long long)need);
   const int64_t N = c->n;
   hipStream_t s = c->stream;
-  std::vector<uint8_t> host((size_t)need);
+  // small or host-made fields go through a host copy, the others from the device
+  // array that holds them straight to dst
+  std::vector<uint8_t> host;
   auto deliver = [&](const void* src_host) -> pd_status {
     if (dst_on_device)
       HIPCHK(c, hipMemcpyAsync(dst, src_host, (size_t)need, hipMemcpyHostToDevice, s));
@@ -1563,47 +1565,43 @@ pd_status pd_get(pd_ctx* c, pd_field f, void* dst, int64_t dst_bytes, int32_t ds
     HIPCHK(c, hipStreamSynchronize(s));
     return PD_OK;
   };
-  auto soa_from_dev = [&](const double* d) -> pd_status {
-    HIPCHK(c, hipMemcpyAsync(host.data(), d, (size_t)need, hipMemcpyDeviceToHost, s));
+  auto from_dev = [&](const void* d) -> pd_status {
+    if (need)
+      HIPCHK(c, hipMemcpyAsync(dst, d, (size_t)need, dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
-    return deliver(host.data());
+    return PD_OK;
+  };
+  // a field that a kernel makes: into dst itself, or by way of the field buffer
+  auto made = [&](auto launch) -> pd_status {
+    if (dst_on_device) {
+      HIPCHK(c, launch(static_cast<double*>(dst)));
+      HIPCHK(c, hipStreamSynchronize(s));
+      return PD_OK;
+    }
+    if (!c->F) TRY(alloc_n(c, &c->F, 3 * N, "field output"));
+    HIPCHK(c, launch(c->F));
+    return from_dev(c->F);
   };
   switch (f) {
-    case PD_DISPLACEMENT: {
-      std::vector<double4> u4((size_t)N);
-      HIPCHK(c, hipMemcpyAsync(u4.data(), c->u4[c->cur], sizeof(double4) * N, hipMemcpyDeviceToHost, s));
-      HIPCHK(c, hipStreamSynchronize(s));
-      double* o = reinterpret_cast<double*>(host.data());
-      for (int64_t i = 0; i < N; ++i) {
-        o[i] = u4[i].x;
-        o[N + i] = u4[i].y;
-        o[2 * N + i] = u4[i].z;
-      }
-      return deliver(host.data());
-    }
-    case PD_VELOCITY: return soa_from_dev(c->v);
-    case PD_ACCEL: return soa_from_dev(c->a);
+    case PD_DISPLACEMENT:
+      return made([&](double* o) { return launch_unpack_u(c->u4[c->cur], o, N, s); });
+    case PD_VELOCITY: return from_dev(c->v);
+    case PD_ACCEL: return from_dev(c->a);
     case PD_FORCE_DENSITY: {
-      if (!c->F) TRY(alloc_n(c, &c->F, 3 * N, "force output"));
+      if (!c->F) TRY(alloc_n(c, &c->F, 3 * N, "field output"));
       TRY(sync_columns(c));  // the force-only pass reads the bond memory from the column words
       StepArgs A = step_args(c);
       HIPCHK(c, launch_wall_corners(A, 1, s));
       HIPCHK(c, launch_step(A, MODE_FORCE_ONLY, s));
-      return soa_from_dev(c->F);
+      return from_dev(c->F);
     }
-    case PD_DAMAGE: case PD_INTACT_COUNT: case PD_INITIAL_COUNT: {
-      std::vector<int32_t> it((size_t)N), n0((size_t)N);
-      HIPCHK(c, hipMemcpyAsync(it.data(), c->intact, 4 * N, hipMemcpyDeviceToHost, s));
-      HIPCHK(c, hipMemcpyAsync(n0.data(), c->rowlen, 4 * N, hipMemcpyDeviceToHost, s));
-      HIPCHK(c, hipStreamSynchronize(s));
-      if (f == PD_INTACT_COUNT) return deliver(it.data());
-      if (f == PD_INITIAL_COUNT) return deliver(n0.data());
-      double* o = reinterpret_cast<double*>(host.data());
-      for (int64_t i = 0; i < N; ++i) o[i] = n0[i] > 0 ? 1.0 - (double)it[i] / (double)n0[i] : 0.0;
-      return deliver(host.data());
-    }
+    case PD_DAMAGE:
+      return made([&](double* o) { return launch_damage(c->intact, c->rowlen, o, N, s); });
+    case PD_INTACT_COUNT: return from_dev(c->intact);
+    case PD_INITIAL_COUNT: return from_dev(c->rowlen);
     case PD_BOND_ROWPTR: case PD_BOND_COL: case PD_BOND_BROKEN: {
       TRY(sync_columns(c));
+      host.resize((size_t)need);
       std::vector<int32_t> rl((size_t)N);
       std::vector<uint32_t> col((size_t)c->padded);
       const uint32_t node_mask = (1u << c->node_bits) - 1u;
@@ -1628,22 +1626,18 @@ pd_status pd_get(pd_ctx* c, pd_field f, void* dst, int64_t dst_bytes, int32_t ds
       if (f == PD_BOND_ROWPTR) reinterpret_cast<int64_t*>(host.data())[N] = e;
       return deliver(host.data());
     }
-    case PD_CONTACT_ROWPTR: case PD_CONTACT_COL: {
+    case PD_CONTACT_ROWPTR: {
+      host.resize((size_t)need);
       std::vector<int32_t> cp((size_t)N + 1);
       HIPCHK(c, hipMemcpyAsync(cp.data(), c->cand_ptr, 4 * (N + 1), hipMemcpyDeviceToHost, s));
       HIPCHK(c, hipStreamSynchronize(s));
-      if (f == PD_CONTACT_ROWPTR) {
-        int64_t* o = reinterpret_cast<int64_t*>(host.data());
-        for (int64_t i = 0; i <= N; ++i) o[i] = cp[(size_t)i];
-        return deliver(host.data());
-      }
-      if (need > 0) {
-        HIPCHK(c, hipMemcpyAsync(host.data(), c->cand, (size_t)need, hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipStreamSynchronize(s));
-      }
+      int64_t* o = reinterpret_cast<int64_t*>(host.data());
+      for (int64_t i = 0; i <= N; ++i) o[i] = cp[(size_t)i];
       return deliver(host.data());
     }
+    case PD_CONTACT_COL: return from_dev(c->cand);
     case PD_WALL_FORCE: case PD_WALL_OFFSET: case PD_WALL_IMPULSE: {
+      host.resize((size_t)need);
       std::vector<WallDev> w((size_t)std::max(c->n_walls, 1));
       if (c->n_walls) {
         HIPCHK(c, hipMemcpyAsync(w.data(), c->walls, sizeof(WallDev) * c->n_walls, hipMemcpyDeviceToHost, s));
@@ -1670,11 +1664,10 @@ pd_status pd_get(pd_ctx* c, pd_field f, void* dst, int64_t dst_bytes, int32_t ds
       StepArgs A = step_args(c);
       HIPCHK(c, launch_energy(A, c->energy_partial, nb, s));
       HIPCHK(c, launch_reduce_energy(c->energy_partial, nb, c->energy_out, s));
-      return soa_from_dev(c->energy_out);
+      return from_dev(c->energy_out);
     }
     case PD_STEP: {
-      memcpy(host.data(), &c->step, 8);
-      return deliver(host.data());
+      return deliver(&c->step);
     }
   }
   return fail(c, PD_ERR_INVALID, "unknown field %d", (int)f);

@@ -312,6 +312,9 @@ hipError_t scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* scratch
 hipError_t scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t s);
 int32_t step_grid_blocks(int64_t nslices);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
+// fields of pd_get: u as SoA, damage 1 - intact / initial (0 where initial = 0)
+hipError_t launch_unpack_u(const double4* u4, double* out, int64_t n, hipStream_t s);
+hipError_t launch_damage(const int32_t* intact, const int32_t* initial, double* out, int64_t n, hipStream_t s);
 // X4[i] = (X[i], X[n + i], X[2n + i], 0)
 hipError_t launch_pack_x4(const double* X, double4* X4, int64_t n, hipStream_t s);
 // tiled bond loop: MODE_STEP over all tiles (events as for launch_step_spb)

@@ -1856,6 +1856,37 @@ __global__ void k_pack_x4(const double* X, double4* X4, int64_t n) {
   if (i < n) X4[i] = make_double4(X[i], X[n + i], X[2 * n + i], 0.0);
 }
 
+// the fields of pd_get that are not stored the way they are handed out, made on
+// the device (56 bytes of u and 16 of counts per node at copy rate; taken through
+// host memory, u of 9.26 million nodes cost about 80 ms)
+__global__ void k_unpack_u(const double4* u4, double* out, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double4 u = u4[i];
+  out[i] = u.x;
+  out[n + i] = u.y;
+  out[2 * n + i] = u.z;
+}
+
+__global__ void k_damage(const int32_t* intact, const int32_t* initial, double* out, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int32_t n0 = initial[i];
+  out[i] = n0 > 0 ? 1.0 - (double)intact[i] / (double)n0 : 0.0;
+}
+
+hipError_t launch_unpack_u(const double4* u4, double* out, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_unpack_u, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, u4, out, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_damage(const int32_t* intact, const int32_t* initial, double* out, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_damage, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, intact, initial, out, n);
+  return hipGetLastError();
+}
+
 __global__ void k_fill_i32_kernel(int32_t* p, int32_t v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
