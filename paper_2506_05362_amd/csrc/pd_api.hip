@@ -98,19 +98,18 @@ struct pd_ctx {
   // contact
   uint32_t T = 0;
   int64_t capacity = 0;
-  long long* cellkey = nullptr;
-  int4* srec = nullptr;
+  int4 *rec = nullptr, *srec = nullptr, *spos = nullptr;
+  int32_t* grain_begin_d = nullptr;
+  double* origin = nullptr;
   int32_t* cand_scratch = nullptr;
   int32_t scratch_w = 32;
-  int32_t *bucket_count = nullptr, *bucket_start = nullptr, *bucket_fill = nullptr,
-          *cand_ptr = nullptr, *cand = nullptr;
+  int32_t *rank = nullptr, *bucket_count = nullptr, *bucket_start = nullptr, *bucket_top = nullptr,
+          *celltag = nullptr, *cand_count = nullptr, *cand_top = nullptr, *cand_ptr = nullptr, *cand = nullptr;
   uint32_t* cellh = nullptr;
   int64_t* grid = nullptr;  // [8] cell grid of the last rebuild
   double* u_build = nullptr;
   long long* gbox = nullptr;
-  int32_t *gpair_count = nullptr, *gpair = nullptr;
-  uint8_t* active = nullptr;
-  int32_t* scan32 = nullptr;
+  int32_t* isolated = nullptr;
   int64_t* scan64 = nullptr;
   double* energy_partial = nullptr;
   double* scratch_dev = nullptr;  // this context's GPU's copy of the allocation-free scratch
@@ -366,22 +365,26 @@ ContactArgs contact_args(pd_ctx* c, int buf) {
   C.u = c->u4[buf];
   C.X = c->X;
   C.X4 = c->X4;
-  C.cellkey = c->cellkey;
+  C.rec = c->rec;
+  C.spos = c->spos;
+  C.grain_begin = c->grain_begin_d;
+  C.origin = c->origin;
   C.srec = c->srec;
   C.cand_scratch = c->cand_scratch;
   C.scratch_w = c->scratch_w;
   C.cellh = c->cellh;
   C.bucket_count = c->bucket_count;
   C.bucket_start = c->bucket_start;
-  C.bucket_fill = c->bucket_fill;
-  C.cand_count = c->cand_ptr;
+  C.bucket_top = c->bucket_top;
+  C.rank = c->rank;
+  C.celltag = c->celltag;
+  C.cand_count = c->cand_count;
+  C.cand_top = c->cand_top;
+  C.cand_ptr = c->cand_ptr;
   C.cand = c->cand;
   C.u_build = c->u_build;
-  C.scan_scratch = c->scan32;
   C.gbox = c->gbox;
-  C.gpair_count = c->gpair_count;
-  C.gpair = c->gpair;
-  C.active = c->active;
+  C.isolated = c->isolated;
   C.box_chunks = c->box_chunks;
   C.n_box_chunks = c->n_box_chunks;
   C.n_grains = c->n_grains;
@@ -1308,30 +1311,43 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
   c->T = T;
   c->capacity = std::max<int64_t>((int64_t)c->cap_per_node * N, 1 << 16);
   c->scratch_w = 2 * c->cap_per_node;
-  TRY(alloc_n(c, &c->cellkey, N, "cell keys"));
+  TRY(alloc_n(c, &c->rec, 2 * N, "node records"));
+  TRY(alloc_n(c, &c->spos, N, "binned positions"));
+  TRY(alloc_n(c, &c->origin, 4, "cell grid origin"));
+  TRY(alloc_n(c, &c->rank, N, "ranks in buckets"));
   TRY(alloc_n(c, &c->srec, N, "binned records"));
   TRY(alloc_n(c, &c->cand_scratch, (int64_t)c->scratch_w * N, "candidate scratch rows"));
   TRY(alloc_n(c, &c->cellh, N, "cell hashes"));
   TRY(alloc_n(c, &c->grid, 8, "cell grid"));
-  TRY(alloc_n(c, &c->bucket_count, T, "bucket counts"));
+  TRY(alloc_n(c, &c->bucket_count, (int64_t)T + 1, "bucket counts"));
   TRY(alloc_n(c, &c->bucket_start, (int64_t)T + 1, "bucket starts"));
-  TRY(alloc_n(c, &c->bucket_fill, T, "bucket fill"));
+  TRY(alloc_n(c, &c->bucket_top, scan_scratch_elems((int64_t)T + 1), "bucket tile sums"));
+  TRY(alloc_n(c, &c->celltag, (int64_t)T + 2, "cell tags"));
+  TRY(alloc_n(c, &c->cand_count, N + 1, "candidate counts"));
+  TRY(alloc_n(c, &c->cand_top, scan_scratch_elems(N + 1), "candidate tile sums"));
   TRY(alloc_n(c, &c->cand_ptr, N + 1, "candidate rows"));
   TRY(alloc_n(c, &c->cand, c->capacity, "candidates"));
   TRY(alloc_n(c, &c->u_build, 3 * N, "positions at rebuild"));
-  TRY(alloc_n(c, &c->scan32, scan_scratch_elems(std::max<int64_t>(T, N)), "scan scratch"));
   TRY(alloc_n(c, &c->gbox, 6 * (int64_t)G, "grain boxes"));
-  TRY(alloc_n(c, &c->gpair_count, (int64_t)G + 1, "grain pair counts"));
-  TRY(alloc_n(c, &c->gpair, (int64_t)G * G, "grain pairs"));
-  TRY(alloc_n(c, &c->active, N, "active flags"));
+  TRY(alloc_n(c, &c->isolated, G, "isolated grains"));
+  TRY(alloc_n(c, &c->grain_begin_d, (int64_t)G + 1, "grain node ranges"));
   {
-    // grain-box reduction work: chunks of at most 16384 nodes of one grain
+    const std::vector<int32_t> gb(c->grain_begin.begin(), c->grain_begin.end());
+    HIPCHK(c, hipMemcpyAsync(c->grain_begin_d, gb.data(), sizeof(int32_t) * gb.size(), hipMemcpyHostToDevice, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+  }
+  HIPCHK(c, launch_fill_i32(c->bucket_count, 0, (int64_t)T + 1, s));
+  HIPCHK(c, launch_fill_i32(c->cand_ptr, 0, N + 1, s));
+  {
+    // grain-box reduction work: chunks of at most kBoxChunk nodes of one grain
+    // (eight nodes a thread; at 16384 the nodes of one large grain met on a few CUs)
+    constexpr int64_t kBoxChunk = 2048;
     std::vector<int64_t> ch;
     for (int32_t g = 0; g < G; ++g)
-      for (int64_t b = c->grain_begin[g]; b < c->grain_begin[g + 1]; b += 16384) {
+      for (int64_t b = c->grain_begin[g]; b < c->grain_begin[g + 1]; b += kBoxChunk) {
         ch.push_back(g);
         ch.push_back(b);
-        ch.push_back(std::min<int64_t>(b + 16384, c->grain_begin[g + 1]));
+        ch.push_back(std::min<int64_t>(b + kBoxChunk, c->grain_begin[g + 1]));
       }
     c->n_box_chunks = (int32_t)(ch.size() / 3);
     TRY(alloc_n(c, &c->box_chunks, (int64_t)ch.size(), "box chunks"));

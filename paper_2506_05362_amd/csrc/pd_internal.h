@@ -239,22 +239,25 @@ struct ContactArgs {
   const double4* u;
   const double* X;
   const double4* X4;  // (x, y, z, 0) per node: one load per candidate position
-  long long* cellkey;    // [N] packed cell coordinates of each binned node
-  uint32_t* cellh;       // [N]
-  int32_t* bucket_count;  // [T]
-  int32_t* bucket_start;  // [T+1]
-  int32_t* bucket_fill;   // [T]
-  int4* srec;             // [N] bucket-sorted (node, grain, cell key lo, hi)
+  int4* rec;              // [2N] (node, grain, cell key lo, hi), (FP32 x, y, z from origin, node) of each binned node
+  uint32_t* cellh;        // [N] its bucket
+  int32_t* rank;          // [N] its place in the bucket, -1 for nodes that are not binned
+  int32_t* bucket_count;  // [T+1] zero between rebuilds
+  int32_t* bucket_start;  // [T+1] starts within a scan tile ...
+  int32_t* bucket_top;    // [T / tile + 1] ... and the sums before each tile
+  int32_t* celltag;       // [T+2] what each bucket holds (k_tag), from entry 1
+  int4* srec;             // [N] the first halves in bucket order
+  int4* spos;             // [N] the second halves
   int32_t* cand_scratch;  // [N][scratch_w] unsorted candidates of each node
   int32_t scratch_w;
-  int32_t* cand_count;    // [N+1] (scanned in place to cand_ptr)
+  int32_t* cand_count;    // [N+1] counts, scanned in place within tiles ...
+  int32_t* cand_top;      // [N / tile + 1] ... and the sums before each tile
+  int32_t* cand_ptr;      // [N+1]
   int32_t* cand;
   double* u_build;        // SoA
-  int32_t* scan_scratch;  // >= scan_scratch_elems(max(T, N))
   long long* gbox;        // [G][6] order-preserving encodings of min xyz, max xyz of p
-  int32_t* gpair_count;   // [G+1] (scanned in place)
-  int32_t* gpair;         // [G*G] other grains whose boxes come within the cutoff
-  uint8_t* active;        // [N] node within the cutoff of another grain's box
+  const int32_t* grain_begin;  // [G+1] first node of each grain
+  int32_t* isolated;      // [G] no other grain's box within the cutoff: not binned, no candidates
   const int64_t* box_chunks;  // [n_box_chunks][3]: grain, first node, end node (one grain each)
   int32_t n_box_chunks;
   int32_t n_grains;
@@ -263,11 +266,12 @@ struct ContactArgs {
   int64_t n;
   uint32_t T;             // power of two
   // cell grid of this rebuild (k_grid_setup): [0] 1 when the cells of the box
-  // around all nodes fit in T buckets, which are then the cells themselves in
+  // around all binned nodes fit in T buckets, which are then the cells themselves in
   // lexicographic order (neighbouring cells sit next to each other in memory);
   // otherwise cells are hashed into the T buckets.  [1..3] the box's first
-  // cell, [4..6] its extent in cells.
+  // cell, [4..6] its extent in cells, [7] the buckets in use.
   int64_t* grid;
+  double* origin;         // [4] corner of that box, and the limit of the FP32 distance test, squared
   int64_t capacity;
   double inv_cell;
   double cut2;            // (R_c + skin)^2
@@ -309,7 +313,6 @@ hipError_t launch_fill_u4(double4* u4, const double* u, const int32_t* ijk, cons
 // exclusive scans with a total in out[n]; scratch >= scan_scratch_elems(n) elements
 int64_t scan_scratch_elems(int64_t n);
 hipError_t scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* scratch, hipStream_t s);
-hipError_t scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t s);
 int32_t step_grid_blocks(int64_t nslices);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 // fields of pd_get: u as SoA, damage 1 - intact / initial (0 where initial = 0)

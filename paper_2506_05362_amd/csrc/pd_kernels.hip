@@ -1469,6 +1469,10 @@ __global__ void k_reduce_energy(const double* partial4, int32_t nblocks, double*
   }
 }
 
+constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 4;
+constexpr int kScanTile = kScanThreads * kScanItems;
+
 // ---------------------------------------------------------------------------
 // contact candidates: hashed uniform cell grid, counting sort, per-node rows
 // ---------------------------------------------------------------------------
@@ -1494,10 +1498,8 @@ __device__ __forceinline__ long long cell_key(int cx, int cy, int cz) {
          (long long)(cz + (1 << 20));
 }
 
-// Grain-box culling.  A pair (i, j) of different grains closer than the
-// cutoff needs p_i within the cutoff of grain(j)'s box and p_j within the
-// cutoff of grain(i)'s box, so only nodes within the cutoff of another grain's
-// box ("active" nodes) are binned and searched; the result is unchanged.
+// Grain culling.  A grain whose box comes within the cutoff of no other grain's
+// box ("isolated") has no candidates: its nodes are neither binned nor searched.
 
 __device__ __forceinline__ long long ord_key(double x) {
   const long long b = __double_as_longlong(x);
@@ -1528,16 +1530,38 @@ __device__ __forceinline__ long long wave_max_ll(long long x) {
   return x;
 }
 
-// one workgroup per chunk of a single grain: LDS reduction, then 6 atomics
-__global__ __launch_bounds__(256) void k_box(ContactArgs c) {
-  __shared__ long long red[6][256];
+// Displacement since the last rebuild beyond skin/2 invalidates the list; the
+// positions of this rebuild are kept (a halted step leaves them alone).
+__device__ __forceinline__ void skin_node(const ContactArgs& c, int64_t i, const double4& u, int check) {
+  if (check) {
+    const double dx = u.x - c.u_build[i], dy = u.y - c.u_build[c.n + i], dz = u.z - c.u_build[2 * c.n + i];
+    if (dx * dx + dy * dy + dz * dz > c.skin_half2) atomicOr(c.status, ST_SKIN);
+  }
+  c.u_build[i] = u.x;
+  c.u_build[c.n + i] = u.y;
+  c.u_build[2 * c.n + i] = u.z;
+}
+
+__global__ void k_skin(ContactArgs c, int check) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= c.n || halted(c.halt)) return;
+  skin_node(c, i, c.u[i], check);
+}
+
+// the same and the grain boxes in one pass over the nodes: one workgroup per
+// chunk of a single grain, LDS reduction, then 6 atomics
+__global__ __launch_bounds__(256) void k_skin_box(ContactArgs c, int check) {
+  __shared__ long long red[6][256 / kWave];
   const int tid = threadIdx.x;
+  const bool live = !halted(c.halt);
   const int64_t* ch = c.box_chunks + 3 * (int64_t)blockIdx.x;
   const int g = (int)ch[0];
+  const int64_t e = ch[2];
   long long k[6] = {ord_key(INFINITY), ord_key(INFINITY), ord_key(INFINITY),
                     ord_key(-INFINITY), ord_key(-INFINITY), ord_key(-INFINITY)};
-  for (int64_t i = ch[1] + tid; i < ch[2]; i += 256) {
+  for (int64_t i = ch[1] + tid; i < e; i += 256) {
     const double4 u = c.u[i];
+    if (live) skin_node(c, i, u, check);
     const long long x = ord_key(c.X[i] + u.x), y = ord_key(c.X[c.n + i] + u.y),
                     z = ord_key(c.X[2 * c.n + i] + u.z);
     k[0] = min(k[0], x);
@@ -1547,71 +1571,50 @@ __global__ __launch_bounds__(256) void k_box(ContactArgs c) {
     k[4] = max(k[4], y);
     k[5] = max(k[5], z);
   }
-  for (int q = 0; q < 6; ++q) red[q][tid] = k[q];
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o)
-      for (int q = 0; q < 6; ++q)
-        red[q][tid] = q < 3 ? min(red[q][tid], red[q][tid + o]) : max(red[q][tid], red[q][tid + o]);
-    __syncthreads();
+  for (int q = 0; q < 6; ++q) {
+    const long long w = q < 3 ? wave_min_ll(k[q]) : wave_max_ll(k[q]);
+    if ((tid & 63) == 0) red[q][tid >> 6] = w;
   }
-  if (tid < 3) atomicMin(c.gbox + 6 * g + tid, red[tid][0]);
-  else if (tid < 6) atomicMax(c.gbox + 6 * g + tid, red[tid][0]);
+  __syncthreads();
+  if (tid < 6) {
+    long long w = red[tid][0];
+    for (int v = 1; v < 256 / kWave; ++v) w = tid < 3 ? min(w, red[tid][v]) : max(w, red[tid][v]);
+    if (tid < 3) atomicMin(c.gbox + 6 * g + tid, w);
+    else atomicMax(c.gbox + 6 * g + tid, w);
+  }
 }
 
-// grain boxes closer than the cutoff: one wavefront per grain, the others
-// tested 64 at a time; ballot prefix counts keep each list in ascending order
-template <bool FILL>
-__global__ __launch_bounds__(kWave) void k_box_pairs(ContactArgs c, double cut) {
+// is any other grain's box within the cutoff?  One wavefront per grain, the
+// others tested 64 at a time; with self-contact no grain is isolated.
+__global__ __launch_bounds__(kWave) void k_isolated(ContactArgs c, double cut) {
   const int a = blockIdx.x, lane = threadIdx.x;
   double alo[3], ahi[3];
   for (int q = 0; q < 3; ++q) {
     alo[q] = ord_val(c.gbox[6 * a + q]) - cut;
     ahi[q] = ord_val(c.gbox[6 * a + 3 + q]) + cut;
   }
-  int cnt = 0;
-  const int base = FILL ? c.gpair_count[a] : 0;
-  for (int b0 = 0; b0 < c.n_grains; b0 += kWave) {
+  bool near = c.self_contact && alo[0] <= ahi[0];
+  for (int b0 = 0; b0 < c.n_grains && !near; b0 += kWave) {
     const int b = b0 + lane;
     bool ov = b < c.n_grains && b != a;
     if (ov)
       for (int q = 0; q < 3; ++q)
         ov = ov && ord_val(c.gbox[6 * b + q]) <= ahi[q] && ord_val(c.gbox[6 * b + 3 + q]) >= alo[q];
-    const uint64_t m = __ballot(ov);
-    if (FILL && ov) c.gpair[base + cnt + __popcll(m & ((1ull << lane) - 1ull))] = b;
-    cnt += __popcll(m);
+    near = __ballot(ov) != 0ull;
   }
-  if (!FILL && lane == 0) c.gpair_count[a] = cnt;
+  if (lane == 0) c.isolated[a] = near ? 0 : 1;
 }
 
-__global__ void k_active(ContactArgs c, double cut) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c.n) return;
-  const double4 u = c.u[i];
-  const int g = packed_grain(u.w);
-  const double p[3] = {c.X[i] + u.x, c.X[c.n + i] + u.y, c.X[2 * c.n + i] + u.z};
-  // with self-contact every node can meet a node of its own grain
-  uint8_t act = c.self_contact ? 1 : 0;
-  for (int e = c.gpair_count[g]; e < c.gpair_count[g + 1] && !act; ++e) {
-    const int b = c.gpair[e];
-    bool in = true;
-    for (int q = 0; q < 3; ++q)
-      in = in && p[q] >= ord_val(c.gbox[6 * b + q]) - cut && p[q] <= ord_val(c.gbox[6 * b + 3 + q]) + cut;
-    act = in ? 1 : 0;
-  }
-  c.active[i] = act;
-}
-
-// The cell grid of this rebuild: the box around every node's position (the
-// union of the grain boxes), in cells; dense when its cell count fits the
-// buckets.  One wavefront.
+// The cell grid of this rebuild: the box around the nodes to be binned (the
+// union of the boxes of the grains that are not isolated), in cells; dense when
+// its cell count fits the buckets.  One wavefront.
 __global__ __launch_bounds__(kWave) void k_grid_setup(ContactArgs c) {
   const int lane = threadIdx.x;
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
   for (int g = lane; g < c.n_grains; g += kWave)
     for (int q = 0; q < 3; ++q) {
       const double a = ord_val(c.gbox[6 * g + q]), b = ord_val(c.gbox[6 * g + 3 + q]);
-      if (a <= b) {  // grains without nodes keep an empty box
+      if (a <= b && !c.isolated[g]) {  // grains without nodes keep an empty box
         lo[q] = fmin(lo[q], a);
         hi[q] = fmax(hi[q], b);
       }
@@ -1622,19 +1625,33 @@ __global__ __launch_bounds__(kWave) void k_grid_setup(ContactArgs c) {
       hi[q] = fmax(hi[q], __shfl_xor(hi[q], o, kWave));
     }
   if (lane != 0) return;
-  int64_t dense = 1, cells = 1, o[3], e[3];
+  // (nothing to bin: one empty cell)
+  const bool any = lo[0] <= hi[0] && lo[1] <= hi[1] && lo[2] <= hi[2];
+  int64_t cells = 1, o[3], e[3];
   for (int q = 0; q < 3; ++q) {
-    if (!(lo[q] <= hi[q])) dense = 0;
-    o[q] = dense ? cell_coord(lo[q], c.inv_cell) : 0;
-    e[q] = dense ? cell_coord(hi[q], c.inv_cell) - o[q] + 1 : 1;
-    cells *= e[q];
+    o[q] = any ? cell_coord(lo[q], c.inv_cell) : 0;
+    e[q] = any ? cell_coord(hi[q], c.inv_cell) - o[q] + 1 : 1;
+    cells = cells <= (int64_t)c.T ? cells * e[q] : cells;
   }
-  if (cells > (int64_t)c.T) dense = 0;
-  c.grid[0] = dense;
+  const bool dense = cells <= (int64_t)c.T;
+  c.grid[0] = dense ? 1 : 0;
   for (int q = 0; q < 3; ++q) {
     c.grid[1 + q] = o[q];
     c.grid[4 + q] = e[q];
   }
+  c.grid[7] = dense ? cells : (int64_t)c.T;
+  // The search's first test is in FP32 on positions relative to the box corner.
+  // With extents up to M a stored coordinate is off by at most 2^-24 M and the
+  // distance of two nodes by less than 8 * 2^-24 M (1 + 2^-20), so that no pair
+  // within the cutoff lies beyond this limit; the pairs it lets through are
+  // tested exactly.
+  double M = 0.0;
+  for (int q = 0; q < 3; ++q) {
+    c.origin[q] = any ? lo[q] : 0.0;
+    M = any ? fmax(M, hi[q] - lo[q]) : M;
+  }
+  const double lim = (sqrt(c.cut2) + M * 0x1p-21) * (1.0 + 1e-5);
+  c.origin[3] = lim * lim;
 }
 
 // bucket of a cell: its lexicographic index in the dense grid, else its hash
@@ -1644,108 +1661,313 @@ __device__ __forceinline__ uint32_t cell_bucket(const ContactArgs& c, bool dense
   return cell_hash(cx, cy, cz, c.T);
 }
 
+// The atomic that counts a bucket's nodes also numbers them, so that the
+// scatter needs no second one.
 __global__ void k_bin(ContactArgs c) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c.n || !c.active[i]) return;
+  if (i >= c.n) return;
   const double4 u = c.u[i];
+  const int g = packed_grain(u.w);
+  if (c.isolated[g]) {
+    c.rank[i] = -1;
+    c.cand_count[i] = 0;
+    return;
+  }
   const int cx = cell_coord(c.X[i] + u.x, c.inv_cell);
   const int cy = cell_coord(c.X[c.n + i] + u.y, c.inv_cell);
   const int cz = cell_coord(c.X[2 * c.n + i] + u.z, c.inv_cell);
-  c.cellkey[i] = cell_key(cx, cy, cz);
+  const long long key = cell_key(cx, cy, cz);
   const uint32_t hsh = cell_bucket(c, c.grid[0] != 0, cx, cy, cz);
+  c.rec[2 * i] = make_int4((int)i, g, (int)(key & 0xffffffffll), (int)(key >> 32));
+  c.rec[2 * i + 1] = make_int4(__float_as_int((float)(c.X[i] + u.x - c.origin[0])),
+                               __float_as_int((float)(c.X[c.n + i] + u.y - c.origin[1])),
+                               __float_as_int((float)(c.X[2 * c.n + i] + u.z - c.origin[2])), (int)i);
   c.cellh[i] = hsh;
-  atomicAdd(c.bucket_count + hsh, 1);
+  c.rank[i] = atomicAdd(c.bucket_count + hsh, 1);
+}
+
+// first record of bucket b (b up to the number of buckets in use): the scan
+// leaves block-local sums and the sums before each block
+__device__ __forceinline__ int bucket_begin(const ContactArgs& c, int64_t b) {
+  return c.bucket_start[b] + c.bucket_top[b / kScanTile];
 }
 
 __global__ void k_scatter(ContactArgs c) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c.n || !c.active[i]) return;
-  const uint32_t hsh = c.cellh[i];
-  const int pos = c.bucket_start[hsh] + atomicAdd(c.bucket_fill + hsh, 1);
-  const long long key = c.cellkey[i];
-  c.srec[pos] = make_int4((int)i, packed_grain(c.u[i].w), (int)(key & 0xffffffffll), (int)(key >> 32));
+  if (i >= c.n) return;
+  const int r = c.rank[i];
+  if (r < 0) return;
+  const int at = bucket_begin(c, c.cellh[i]) + r;
+  c.srec[at] = c.rec[2 * i];
+  c.spos[at] = c.rec[2 * i + 1];
 }
 
-// Search: every record of the 27 neighbouring cells' buckets is one 16-byte
-// load (node, grain, cell key); records of other cells sharing the bucket and
-// of the node's own grain are skipped before any position is read.  Threads
-// walk the binned nodes in bucket order, so the nodes of one cell sit in
-// neighbouring lanes and read the same buckets.  In a dense grid the three
-// cells of a z-run are consecutive buckets, read as one range (and hold no
-// other cells).  Hits go to a fixed-width scratch row; counts beyond the width
-// raise the overflow flag.  Rows of nodes that were not binned stay at zero
-// (cleared before the launch).
-__device__ __forceinline__ void cand_consider(const ContactArgs& c, const int4& r, int64_t i, int gi, double Xx,
-                                              double Xy, double Xz, const double4& ui, int32_t* row, int& cnt) {
-  // with self-contact the node's own grain counts too (whether a pair is
-  // bonded is decided at the force, from the bond memory)
-  if (r.y == gi && (!c.self_contact || r.x == i)) return;
-  const int j = r.x;
-  const double4 uj = c.u[j];
-  const double* xp = reinterpret_cast<const double*>(c.X4 + j);
-  double yx, yy, yz;
-  const double d2 = contact_d2(xp[0], Xx, uj.x, ui.x, xp[1], Xy, uj.y, ui.y, xp[2], Xz, uj.z, ui.z, yx, yy, yz);
-  if (!(d2 < c.cut2)) return;
-  if (cnt < c.scratch_w) row[cnt] = j;
-  ++cnt;
-}
-
-__global__ __launch_bounds__(256) void k_cand_search(ContactArgs c) {
-  const int64_t e0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e0 >= c.bucket_start[c.T]) return;
-  const int4 me = c.srec[e0];
-  const int64_t i = me.x;
-  const int gi = me.y;
-  const double4 ui = c.u[i];
-  const long long key = ((long long)me.w << 32) | (long long)(uint32_t)me.z;
-  const int cx = (int)((key >> 42) & 0x1fffff) - (1 << 20);
-  const int cy = (int)((key >> 21) & 0x1fffff) - (1 << 20);
-  const int cz = (int)(key & 0x1fffff) - (1 << 20);
-  const double4 Xi = c.X4[i];
-  const double Xx = Xi.x, Xy = Xi.y, Xz = Xi.z;
-  int32_t* row = c.cand_scratch + i * (int64_t)c.scratch_w;
-  int cnt = 0;
-  if (c.grid[0]) {
-    const int64_t ex = c.grid[4], ey = c.grid[5], ez = c.grid[6];
-    const int64_t lx = cx - c.grid[1], ly = cy - c.grid[2], lz = cz - c.grid[3];
-    const int64_t z0 = lz > 0 ? lz - 1 : 0, z1 = lz + 1 < ez ? lz + 1 : ez - 1;
-    for (int d = 0; d < 9; ++d) {
-      const int64_t nx = lx + d / 3 - 1, ny = ly + d % 3 - 1;
-      if (nx < 0 || ny < 0 || nx >= ex || ny >= ey) continue;
-      const int64_t b = (nx * ey + ny) * ez;
-      const int e1 = c.bucket_start[b + z1 + 1];
-      for (int e = c.bucket_start[b + z0]; e < e1; ++e) cand_consider(c, c.srec[e], i, gi, Xx, Xy, Xz, ui, row, cnt);
+// What a bucket holds: kTagEmpty, the grain of all its nodes, or kTagMixed.  Most
+// cells around a node hold nothing but its own grain; a 4-byte tag then stands
+// for all their records.  (One entry more at either end, so that the search can
+// read the three cells of a z-run as one.)
+constexpr int kTagEmpty = -1, kTagMixed = -2;
+__global__ __launch_bounds__(256) void k_tag(ContactArgs c) {
+  const uint32_t nb = (uint32_t)c.grid[7];
+  for (uint32_t b = blockIdx.x * 256 + threadIdx.x; b < nb; b += gridDim.x * 256) {
+    int e = bucket_begin(c, b);
+    const int e1 = bucket_begin(c, b + 1);
+    int tag = kTagEmpty;
+    if (e < e1) {
+      tag = c.srec[e].y;
+      while (++e < e1)
+        if (c.srec[e].y != tag) {
+          tag = kTagMixed;
+          break;
+        }
     }
+    c.celltag[b + 1] = tag;
+  }
+}
+
+// Search: the cells around a node that hold another grain's nodes.  Each workgroup
+// first reads the tags around its records and keeps the nodes with such a cell (in
+// a dense aggregate of 1000 grains, about half), then gives each of those a thread.
+// In a dense grid a z-run of three cells is one range of records, cut to the cells
+// that count.  Bound by the rate at which the vector cache serves 64 lanes' own
+// addresses, so a record is one 16-byte load (FP32 position and node; its grain is
+// told from the node's range), kRecs of them in flight; the nodes of other grains
+// (with self-contact, all but itself) that may lie within the cutoff go to a row in
+// LDS and are tested exactly in a second pass over it, kNear at a time, into the
+// node's fixed-width scratch row.  Threads walk the binned nodes in bucket order,
+// so neighbouring lanes read the same runs.  Counts beyond the scratch row's width
+// raise the overflow flag.  Large aggregate (9.26 million nodes, cutoff 1.45 h):
+// 0.95 ms; one thread per node over every record of the 27 cells, 32 bytes of u and
+// of X each, took 1.89 ms.
+constexpr int kRecs = 6, kNear = 6;
+constexpr int kNearRow = 24;  // entries of a thread's row in LDS; a fuller one is tested record by record
+
+// the exact test of the cnt nodes j(0), j(1), ...: out(node) for each within the cutoff
+template <typename J, typename F>
+__device__ __forceinline__ void near_nodes(const ContactArgs& c, const double4& ui, const double4& Xi, int cnt, J j,
+                                           F out) {
+  for (int q = 0; q < cnt; q += kNear) {
+    int jj[kNear];
+    double4 uj[kNear], Xj[kNear];
+#pragma unroll
+    for (int k = 0; k < kNear; ++k) jj[k] = j(q + k < cnt ? q + k : cnt - 1);
+#pragma unroll
+    for (int k = 0; k < kNear; ++k) {
+      uj[k] = c.u[jj[k]];
+      const double* xp = reinterpret_cast<const double*>(c.X4 + jj[k]);
+      Xj[k] = make_double4(xp[0], xp[1], xp[2], 0.0);
+    }
+#pragma unroll
+    for (int k = 0; k < kNear; ++k) {
+      double yx, yy, yz;
+      const double d2 = contact_d2(Xj[k].x, Xi.x, uj[k].x, ui.x, Xj[k].y, Xi.y, uj[k].y, ui.y, Xj[k].z, Xi.z, uj[k].z,
+                                   ui.z, yx, yy, yz);
+      if (q + k < cnt && d2 < c.cut2) out(jj[k]);
+    }
+  }
+}
+
+// the cell of a record
+__device__ __forceinline__ void record_cell(const int4& r, int& cx, int& cy, int& cz) {
+  const long long key = ((long long)r.w << 32) | (long long)(uint32_t)r.z;
+  cx = (int)((key >> 42) & 0x1fffff) - (1 << 20);
+  cy = (int)((key >> 21) & 0x1fffff) - (1 << 20);
+  cz = (int)(key & 0x1fffff) - (1 << 20);
+}
+
+// Every record that may be a candidate of record me, run by run: f(node) for each
+// that passes the FP32 test.  cells: bit 3 d + q of a dense grid's run d, cell z +
+// q - 1, says that the cell may hold one.
+template <typename F>
+__device__ __forceinline__ void search_runs(const ContactArgs& c, const int4& me, const int4& pi, float lim2,
+                                            uint32_t cells, F f) {
+  int cx, cy, cz;
+  record_cell(me, cx, cy, cz);
+  // the nodes that do not count: those of the node's own grain, with
+  // self-contact only itself (whether a pair is bonded is decided at the force,
+  // from the bond memory)
+  const uint32_t skip0 = c.self_contact ? (uint32_t)me.x : (uint32_t)c.grain_begin[me.y];
+  const uint32_t skipn = c.self_contact ? 1u : (uint32_t)c.grain_begin[me.y + 1] - skip0;
+  const float x = __int_as_float(pi.x), y = __int_as_float(pi.y), z = __int_as_float(pi.z);
+  auto range = [&](int e, int e1, auto keyed, int klo, int khi) {
+    for (; e < e1; e += kRecs) {
+      int4 p[kRecs], r[kRecs];
+#pragma unroll
+      for (int k = 0; k < kRecs; ++k) {
+        const int at = e + k < e1 ? e + k : e1 - 1;
+        p[k] = c.spos[at];
+        if (keyed) r[k] = c.srec[at];
+      }
+#pragma unroll
+      for (int k = 0; k < kRecs; ++k) {
+        const float dx = __int_as_float(p[k].x) - x, dy = __int_as_float(p[k].y) - y, dz = __int_as_float(p[k].z) - z;
+        bool ok = e + k < e1 && (uint32_t)p[k].w - skip0 >= skipn && !(dx * dx + dy * dy + dz * dz > lim2);
+        if (keyed) ok = ok && r[k].z == klo && r[k].w == khi;  // else another cell in the same bucket
+        if (ok) f(p[k].w);
+      }
+    }
+  };
+  if (c.grid[0]) {
+    const int ey = (int)c.grid[5], ez = (int)c.grid[6];
+    const int lx = cx - (int)c.grid[1], ly = cy - (int)c.grid[2], lz = cz - (int)c.grid[3];
+    const uint32_t b0 = ((uint32_t)lx * ey + ly) * ez + lz;
+    int e0[9], e1[9];
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+      const uint32_t m = (cells >> (3 * d)) & 7u;
+      // (a run without a bit is empty; its bounds are read from the node's own cell)
+      const uint32_t b = m ? b0 + (uint32_t)((d / 3 - 1) * ey + (d % 3 - 1)) * ez : b0;
+      e0[d] = bucket_begin(c, m ? b + (uint32_t)(__ffs(m) - 2) : b);
+      e1[d] = m ? bucket_begin(c, b + (uint32_t)(31 - __clz(m))) : e0[d];
+    }
+#pragma unroll
+    for (int d = 0; d < 9; ++d) range(e0[d], e1[d], std::false_type{}, 0, 0);
   } else {
+    const int own = c.self_contact ? kTagEmpty : me.y;
     for (int d = 0; d < kCellDirs; ++d) {
       const int nx = cx + d % 3 - 1, ny = cy + (d / 3) % 3 - 1, nz = cz + d / 9 - 1;
       const long long nkey = cell_key(nx, ny, nz);
-      const int klo = (int)(nkey & 0xffffffffll), khi = (int)(nkey >> 32);
-      const uint32_t hsh = cell_hash(nx, ny, nz, c.T);
-      const int e1 = c.bucket_start[hsh + 1];
-      for (int e = c.bucket_start[hsh]; e < e1; ++e) {
-        const int4 r = c.srec[e];
-        if (r.z != klo || r.w != khi) continue;  // another cell in the same bucket
-        cand_consider(c, r, i, gi, Xx, Xy, Xz, ui, row, cnt);
-      }
+      const uint32_t b = cell_hash(nx, ny, nz, c.T);
+      const int t = c.celltag[b + 1];
+      if (t == kTagEmpty || t == own) continue;
+      range(bucket_begin(c, b), bucket_begin(c, (int64_t)b + 1), std::true_type{}, (int)(nkey & 0xffffffffll),
+            (int)(nkey >> 32));
     }
   }
-  if (cnt > c.scratch_w) {
-    atomicOr(c.status, ST_CAND_OVERFLOW);
-    cnt = c.scratch_w;
-  }
-  c.cand_count[i] = cnt;
 }
 
-// scratch row -> CSR row (ascending; rows past the total capacity are cut and flagged)
+// near: this thread's row in LDS, entries 256 apart
+__device__ __forceinline__ void search_node(const ContactArgs& c, int e0, uint32_t cells, int* near) {
+  const int4 me = c.srec[e0], pi = c.spos[e0];
+  const float lim2 = __double2float_ru(c.origin[3]);
+  const int64_t i = me.x;
+  int32_t* row = c.cand_scratch + i * (int64_t)c.scratch_w;
+  const double4 ui = c.u[i], Xi = c.X4[i];
+  int cnt = 0, kept = 0;
+  auto keep = [&](int j) {
+    if (kept < c.scratch_w) row[kept] = j;
+    ++kept;
+  };
+  search_runs(c, me, pi, lim2, cells, [&](int j) {
+    if (cnt < kNearRow) near[256 * cnt] = j;
+    ++cnt;
+  });
+  if (cnt <= kNearRow) {
+    near_nodes(c, ui, Xi, cnt, [&](int k) { return near[256 * k]; }, keep);
+  } else {
+    search_runs(c, me, pi, lim2, cells, [&](int j) { near_nodes(c, ui, Xi, 1, [&](int) { return j; }, keep); });
+  }
+  if (kept > c.scratch_w) {
+    atomicOr(c.status, ST_CAND_OVERFLOW);
+    kept = c.scratch_w;
+  }
+  c.cand_count[i] = kept;
+}
+
+// per: records of a workgroup / 256.  More of them fill its wavefronts better
+// with the nodes that are left to search, fewer leave more workgroups.
+constexpr int kSearchPer = 4;
+__global__ __launch_bounds__(256) void k_cand_search(ContactArgs c, int per) {
+  __shared__ uint2 list[256 * kSearchPer];
+  __shared__ int near[kNearRow * 256];
+  __shared__ int listed;
+  const int total = bucket_begin(c, c.grid[7]);
+  const int64_t r0 = (int64_t)blockIdx.x * 256 * per;
+  if (r0 >= total) return;
+  if (threadIdx.x == 0) listed = 0;
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const bool dense = c.grid[0] != 0;
+  const int ex = (int)c.grid[4], ey = (int)c.grid[5], ez = (int)c.grid[6];
+  for (int k = 0; k < per; ++k) {
+    const int64_t e0 = r0 + k * 256 + threadIdx.x;
+    bool search = e0 < total;
+    uint32_t cells = 0u;
+    if (search && dense) {
+      const int4 me = c.srec[e0];
+      const int own = c.self_contact ? kTagEmpty : me.y;
+      int cx, cy, cz;
+      record_cell(me, cx, cy, cz);
+      const int lx = cx - (int)c.grid[1], ly = cy - (int)c.grid[2], lz = cz - (int)c.grid[3];
+      const uint32_t b0 = ((uint32_t)lx * ey + ly) * ez + lz;
+      int tag[9][3];
+#pragma unroll
+      for (int d = 0; d < 9; ++d) {  // (no branch: all nine loads at once)
+        const int nx = lx + d / 3 - 1, ny = ly + d % 3 - 1;
+        const bool in = nx >= 0 && ny >= 0 && nx < ex && ny < ey;
+        __builtin_memcpy(tag[d], c.celltag + (in ? ((uint32_t)nx * ey + ny) * ez + lz : b0), sizeof tag[d]);
+        if (!in) tag[d][0] = tag[d][1] = tag[d][2] = kTagEmpty;
+      }
+#pragma unroll
+      for (int d = 0; d < 9; ++d)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const bool in = (q != 0 || lz > 0) && (q != 2 || lz + 1 < ez);
+          cells |= (in && tag[d][q] != kTagEmpty && tag[d][q] != own ? 1u : 0u) << (3 * d + q);
+        }
+      search = cells != 0u;
+      if (!search) c.cand_count[me.x] = 0;
+    }
+    const uint64_t m = __ballot(search);
+    if (m) {
+      int at = 0;
+      if (lane == __ffsll((unsigned long long)m) - 1) at = atomicAdd(&listed, __popcll(m));
+      at = __shfl(at, __ffsll((unsigned long long)m) - 1, kWave) + __popcll(m & ((1ull << lane) - 1ull));
+      if (search) list[at] = make_uint2((uint32_t)e0, cells);
+    }
+  }
+  __syncthreads();
+  const int n = listed;
+  for (int q = threadIdx.x; q < n; q += 256) search_node(c, (int)list[q].x, list[q].y, near + threadIdx.x);
+}
+
+// ascending order of N values in registers (Batcher's odd-even merge network)
+template <int N>
+__device__ __forceinline__ void sort_network(int (&v)[N]) {
+#pragma unroll
+  for (int p = 1; p < N; p *= 2)
+#pragma unroll
+    for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+      for (int j = k % p; j <= N - 1 - k; j += 2 * k)
+#pragma unroll
+        for (int i = 0; i < k; ++i)
+          if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+            const int lo = min(v[i + j], v[i + j + k]), hi = max(v[i + j], v[i + j + k]);
+            v[i + j] = lo;
+            v[i + j + k] = hi;
+          }
+}
+
+// scratch row -> CSR row (ascending; rows past the total capacity are cut and
+// flagged).  Rows of up to kSortRow candidates, nearly all of them, are read
+// with every load in flight and sorted in registers; longer ones by insertion.
+constexpr int kSortRow = 16;
 __global__ __launch_bounds__(256) void k_cand_compact(ContactArgs c) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c.n) return;
-  const int64_t base = c.cand_count[i];  // scanned row pointers
-  const int cnt = (int)(c.cand_count[i + 1] - base);
+  if (i > c.n) return;
+  const int64_t base = c.cand_count[i] + c.cand_top[i / kScanTile];
+  c.cand_ptr[i] = (int32_t)base;
+  if (i == c.n) {
+    if (base > c.capacity) atomicOr(c.status, ST_CAND_OVERFLOW);
+    return;
+  }
+  const int cnt = (int)(c.cand_count[i + 1] + c.cand_top[(i + 1) / kScanTile] - base);
   if (cnt == 0) return;
   const int32_t* row = c.cand_scratch + i * (int64_t)c.scratch_w;
   const int64_t end = base + cnt < c.capacity ? base + cnt : c.capacity;
+  if (cnt <= kSortRow && end == base + cnt) {
+    int v[kSortRow];
+#pragma unroll
+    for (int k = 0; k < kSortRow; ++k) v[k] = row[k < cnt ? k : cnt - 1];
+#pragma unroll
+    for (int k = 0; k < kSortRow; ++k) v[k] = k < cnt ? v[k] : INT32_MAX;
+    sort_network(v);
+#pragma unroll
+    for (int k = 0; k < kSortRow; ++k)
+      if (k < cnt) c.cand[base + k] = v[k];
+    return;
+  }
   for (int64_t a = base; a < end; ++a) {
     const int32_t x = row[a - base];
     int64_t q = a - 1;
@@ -1755,25 +1977,6 @@ __global__ __launch_bounds__(256) void k_cand_compact(ContactArgs c) {
     }
     c.cand[q + 1] = x;
   }
-}
-
-__global__ void k_cand_capacity(ContactArgs c) {
-  if (threadIdx.x == 0 && blockIdx.x == 0 && (int64_t)c.cand_count[c.n] > c.capacity)
-    atomicOr(c.status, ST_CAND_OVERFLOW);
-}
-
-// displacement since the last rebuild beyond skin/2 invalidates the list
-__global__ void k_skin(ContactArgs c, int check) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c.n || halted(c.halt)) return;
-  const double4 u = c.u[i];
-  if (check) {
-    const double dx = u.x - c.u_build[i], dy = u.y - c.u_build[c.n + i], dz = u.z - c.u_build[2 * c.n + i];
-    if (dx * dx + dy * dy + dz * dz > c.skin_half2) atomicOr(c.status, ST_SKIN);
-  }
-  c.u_build[i] = u.x;
-  c.u_build[c.n + i] = u.y;
-  c.u_build[2 * c.n + i] = u.z;
 }
 
 __global__ void k_fill_u4(double4* u4, const double* u, const int32_t* ijk, const int64_t* grain_of,
@@ -1788,10 +1991,6 @@ __global__ void k_fill_u4(double4* u4, const double* u, const int32_t* ijk, cons
 // ---------------------------------------------------------------------------
 // exclusive scans (3 passes: block-local, block sums, add)
 // ---------------------------------------------------------------------------
-
-constexpr int kScanThreads = 1024;
-constexpr int kScanItems = 4;
-constexpr int kScanTile = kScanThreads * kScanItems;
 
 template <typename T>
 __device__ T block_inclusive_scan(T x, T* s) {
@@ -1841,6 +2040,56 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_top(T* block_sums, int64_
     carry += chunk;
   }
   if (threadIdx.x == 0) *total = carry;
+}
+
+// The rebuild's two scans, over n values that only the device knows: the same
+// two passes, without the third - readers add the block's sum themselves.
+// Buckets (n = those in use, one more value as the end): the counts are cleared
+// as they are read, so they are zero when the next rebuild bins.  Candidate
+// counts: in place, the value past the last node is the end.
+template <bool BUCKETS>
+__global__ __launch_bounds__(kScanThreads) void k_scan_rebuild(ContactArgs c) {
+  __shared__ int32_t s[kScanThreads];
+  const int64_t n = BUCKETS ? c.grid[7] : c.n;
+  const int64_t tile0 = (int64_t)blockIdx.x * kScanTile;
+  if (tile0 > n) return;
+  const int64_t base = tile0 + (int64_t)threadIdx.x * kScanItems;
+  int32_t* in = BUCKETS ? c.bucket_count : c.cand_count;
+  int32_t* out = BUCKETS ? c.bucket_start : c.cand_count;
+  int32_t v[kScanItems], tot = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) v[k] = in[base + k < n ? base + k : n - 1];
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    v[k] = base + k < n ? v[k] : 0;
+    tot += v[k];
+  }
+  const int32_t inc = block_inclusive_scan(tot, s);
+  int32_t run = inc - tot;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    if (base + k <= n) out[base + k] = run;
+    if (BUCKETS && base + k < n) in[base + k] = 0;
+    run += v[k];
+  }
+  if (threadIdx.x == kScanThreads - 1) (BUCKETS ? c.bucket_top : c.cand_top)[blockIdx.x] = inc;
+}
+
+template <bool BUCKETS>
+__global__ __launch_bounds__(kScanThreads) void k_scan_rebuild_top(ContactArgs c) {
+  __shared__ int32_t s[kScanThreads];
+  const int64_t nb = (BUCKETS ? c.grid[7] : c.n) / kScanTile + 1;
+  int32_t* sums = BUCKETS ? c.bucket_top : c.cand_top;
+  int32_t carry = 0;
+  for (int64_t b = 0; b < nb; b += kScanThreads) {
+    const int64_t idx = b + threadIdx.x;
+    const int32_t x = idx < nb ? sums[idx] : 0;
+    const int32_t inc = block_inclusive_scan(x, s);
+    if (idx < nb) sums[idx] = carry + inc - x;
+    const int32_t chunk = s[kScanThreads - 1];
+    __syncthreads();
+    carry += chunk;
+  }
 }
 
 template <typename T>
@@ -1928,10 +2177,6 @@ static hipError_t scan_impl(const T* in, T* out, int64_t n, T* scratch, hipStrea
 hipError_t scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* scratch, hipStream_t s) {
   return scan_impl<int64_t>(in, out, n, scratch, s);
 }
-hipError_t scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t s) {
-  return scan_impl<int32_t>(in, out, n, scratch, s);
-}
-
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
@@ -2064,29 +2309,27 @@ hipError_t launch_skin_watch(const ContactArgs& c, uint32_t* halt, hipStream_t s
 hipError_t launch_contact_rebuild(const ContactArgs& c, int check_skin, hipStream_t s) {
   if (c.n == 0) return hipSuccess;
   const unsigned g = grid_for(c.n, 256);
+  if (c.n_grains == 1 && !c.self_contact) {  // nothing can touch: only the positions of the rebuild are kept
+    hipLaunchKernelGGL(k_skin, dim3(g), dim3(256), 0, s, c, check_skin);
+    return hipGetLastError();
+  }
   const double cut = sqrt(c.cut2) * (1.0 + 1e-9) + 1e-300;  // boxes inflated by the cutoff
-  hipError_t e;
-  // clears by kernel (not memset nodes) so the sequence can live in a captured graph
-  if ((e = launch_fill_i32(c.bucket_count, 0, (int64_t)c.T, s)) != hipSuccess) return e;
-  if ((e = launch_fill_i32(c.bucket_fill, 0, (int64_t)c.T, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_skin, dim3(g), dim3(256), 0, s, c, check_skin);
-  hipLaunchKernelGGL(k_box_init, dim3(grid_for(6 * (int64_t)c.n_grains, 256)), dim3(256), 0, s, c);
-  hipLaunchKernelGGL(k_box, dim3((unsigned)c.n_box_chunks), dim3(256), 0, s, c);
   const unsigned gg = (unsigned)c.n_grains;
-  hipLaunchKernelGGL(k_box_pairs<false>, dim3(gg), dim3(kWave), 0, s, c, cut);
-  if ((e = scan_i32(c.gpair_count, c.gpair_count, c.n_grains, c.scan_scratch, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_box_pairs<true>, dim3(gg), dim3(kWave), 0, s, c, cut);
-  hipLaunchKernelGGL(k_active, dim3(g), dim3(256), 0, s, c, cut);
+  hipLaunchKernelGGL(k_box_init, dim3(grid_for(6 * (int64_t)c.n_grains, 256)), dim3(256), 0, s, c);
+  hipLaunchKernelGGL(k_skin_box, dim3((unsigned)c.n_box_chunks), dim3(256), 0, s, c, check_skin);
+  hipLaunchKernelGGL(k_isolated, dim3(gg), dim3(kWave), 0, s, c, cut);
   hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kWave), 0, s, c);
   hipLaunchKernelGGL(k_bin, dim3(g), dim3(256), 0, s, c);
-  if ((e = scan_i32(c.bucket_count, c.bucket_start, (int64_t)c.T, c.scan_scratch, s)) != hipSuccess)
-    return e;
+  hipLaunchKernelGGL(k_scan_rebuild<true>, dim3((unsigned)((int64_t)c.T / kScanTile + 1)), dim3(kScanThreads), 0, s, c);
+  hipLaunchKernelGGL(k_scan_rebuild_top<true>, dim3(1), dim3(kScanThreads), 0, s, c);
   hipLaunchKernelGGL(k_scatter, dim3(g), dim3(256), 0, s, c);
-  if ((e = launch_fill_i32(c.cand_count, 0, c.n, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_cand_search, dim3(g), dim3(256), 0, s, c);
-  if ((e = scan_i32(c.cand_count, c.cand_count, c.n, c.scan_scratch, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_cand_capacity, dim3(1), dim3(64), 0, s, c);
-  hipLaunchKernelGGL(k_cand_compact, dim3(g), dim3(256), 0, s, c);
+  hipLaunchKernelGGL(k_tag, dim3(std::min(grid_for((int64_t)c.T, 256), 8192u)), dim3(256), 0, s, c);
+  // four records a thread once that still leaves every CU eight wavefronts a SIMD
+  const int per = c.n >= (int64_t)256 * kSearchPer * 2048 ? kSearchPer : 1;
+  hipLaunchKernelGGL(k_cand_search, dim3(grid_for(c.n, 256 * per)), dim3(256), 0, s, c, per);
+  hipLaunchKernelGGL(k_scan_rebuild<false>, dim3((unsigned)(c.n / kScanTile + 1)), dim3(kScanThreads), 0, s, c);
+  hipLaunchKernelGGL(k_scan_rebuild_top<false>, dim3(1), dim3(kScanThreads), 0, s, c);
+  hipLaunchKernelGGL(k_cand_compact, dim3(grid_for(c.n + 1, 256)), dim3(256), 0, s, c);
   return hipGetLastError();
 }
 
