@@ -1,12 +1,13 @@
-"""Coefficients of the bond-law polynomial used by the step kernels.
+"""Coefficients of the bond-law polynomials used by the step kernels.
 
 The bond force of Sec. 3.1 needs g(x) = 1 - (1 + x)^(-1/2) with
 x = (|y|^2 - |xi|^2) / |xi|^2.  For |x| <= 0.02 the kernels evaluate
-g = x * q(x) with q a degree-8 polynomial: the interpolant of
-q(x) = (1 - (1 + x)^(-1/2)) / x at the nine Chebyshev nodes of [-0.02, 0.02],
-computed here in 80-digit decimal arithmetic.  Its constant term is exactly
-1/2; with the other eight coefficients rounded to double its relative error
-on the interval is about 1e-18 (the ten-term Taylor series: 3.5e-18).
+g = x * q(x) with q a polynomial: the interpolant of
+q(x) = (1 - (1 + x)^(-1/2)) / x at the Chebyshev nodes of the interval, computed
+here in 80-digit decimal arithmetic: degree 6 where |x| <= 0.0055, degree 8 on the
+rest.  Their constant terms are exactly 1/2; with the other coefficients rounded
+to double the relative errors are about 9e-19 and 1e-18 (the ten-term Taylor
+series: 3.5e-18).
 
     python paper_2506_05362_amd/csrc/bond_series.py
 prints the coefficients (highest degree first, as C hex literals) and the
@@ -15,8 +16,6 @@ error of the rounded polynomial on a 801-point grid.
 from decimal import Decimal as D, getcontext
 
 getcontext().prec = 80
-R = D("0.02")
-N = 9
 PI = D("3.14159265358979323846264338327950288419716939937510582097494459230781640628620899")
 
 
@@ -51,12 +50,12 @@ def solve(A, b):
     return x
 
 
-def coefficients():
+def coefficients(R, N):
     xs = [R * cos((2 * k + 1) * PI / (2 * N)) for k in range(N)]
     return solve([[x ** j for j in range(N)] for x in xs], [q(x) for x in xs])
 
 
-def max_rel_error(cs):
+def max_rel_error(cs, R):
     worst = D(0)
     for k in range(-400, 401):
         x = R * k / 400
@@ -68,8 +67,9 @@ def max_rel_error(cs):
 
 
 if __name__ == "__main__":
-    co = coefficients()
-    rounded = [D(float(c)) for c in co]
-    print("constant term:", float(co[0]))
-    print("c8..c1:", ", ".join(float(c).hex() for c in reversed(co[1:])))
-    print("max relative error, rounded coefficients: %.3e" % max_rel_error(rounded))
+    for R, N in ((D("0.0055"), 7), (D("0.02"), 9)):
+        co = coefficients(R, N)
+        rounded = [D(float(c)) for c in co]
+        print("|x| <= %s: constant term" % R, float(co[0]))
+        print("c%d..c1:" % (N - 1), ", ".join(float(c).hex() for c in reversed(co[1:])))
+        print("max relative error, rounded coefficients: %.3e" % max_rel_error(rounded, R))

@@ -133,6 +133,7 @@ struct pd_ctx {
   TileGrain* tgrain = nullptr;
   int32_t* tmap = nullptr;
   StencilC* ttab = nullptr;
+  TileNorms* tnorm = nullptr;
   int16_t* ctob = nullptr;  // [6][n_stencil]: slice-path class -> mask bit per axis order
   double* corner_gl = nullptr;  // Gauss-Legendre nodes and weights on [0, pi] (wall corners)
   uint32_t* corner_w = nullptr;  // [N]
@@ -355,6 +356,7 @@ StepArgs step_args(pd_ctx* c) {
   A.tgrain = c->tgrain;
   A.tmap = c->tmap;
   A.ttab = c->ttab;
+  A.tnorm = c->tnorm;
   A.lmask = c->lmask;
   A.slot = c->slot;
   return A;
@@ -822,6 +824,7 @@ pd_status build_tiles(pd_ctx* c) {
         }
   }
   std::vector<StencilC> ttab((size_t)n_tables * kTileClasses);
+  std::vector<TileNorms> tnorm((size_t)n_tables);
   for (int p = 0; p < 6; ++p)
     for (int cl = 0; cl < c->n_classes; ++cl) {
       const int t = table_of[(size_t)p * c->n_classes + cl];
@@ -829,6 +832,22 @@ pd_status build_tiles(pd_ctx* c) {
       for (int K = 0; K < kTileClasses; ++K)
         ttab[(size_t)t * kTileClasses + K] =
             c->stencil_h[(size_t)cl * (c->n_stencil + 1) + btoc[(size_t)p][(size_t)K]];
+      TileNorms& tn = tnorm[(size_t)t];
+      for (int k = 0; k < c->n_stencil; ++k) {
+        const int* d = &c->sd_h[(size_t)3 * k];
+        const StencilC& r = c->stencil_h[(size_t)cl * (c->n_stencil + 1) + k];
+        const int q = tile_norm(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        tn.bond[q][0] = r.inv_l0sq;
+        tn.bond[q][1] = r.civ;
+        tn.l0[q] = r.l0;
+        tn.l0sq[q] = r.l0sq;
+        if (d[0] > 0 && d[1] == 0 && d[2] == 0) tn.h[d[0]] = r.hx;
+      }
+      for (const GrainC& gc : c->grains_h)
+        if (gc.cls == cl) {
+          tn.thr_x = gc.thr_x;
+          tn.lo_x = gc.lo_x;
+        }
     }
   hipStream_t s = c->stream;
   c->n_tiles = (int64_t)tiles.size();
@@ -836,15 +855,19 @@ pd_status build_tiles(pd_ctx* c) {
   TRY(alloc_n(c, &c->tgrain, std::max<int64_t>((int64_t)rec.size(), 1), "tile boxes"));
   TRY(alloc_n(c, &c->tmap, std::max<int64_t>(map_total, 1), "tile cell map"));
   TRY(alloc_n(c, &c->ttab, std::max<int64_t>((int64_t)ttab.size(), 1), "tile bond tables"));
+  TRY(alloc_n(c, &c->tnorm, std::max<int64_t>(n_tables, 1), "tile bond constants"));
   TRY(alloc_n(c, &c->ctob, std::max<int64_t>((int64_t)ctob.size(), 1), "class to mask bit"));
   if ((int64_t)tiles.size() * kTS * kWave >= ((int64_t)1 << 31))
     return fail(c, PD_ERR_UNSUPPORTED, "%lld tiles exceed the 31-bit node slots", (long long)tiles.size());
-  TRY(alloc_n(c, &c->lmask, std::max<int64_t>((int64_t)tiles.size() * kTS * kTileClasses, 1), "lane masks"));
+  // (a few masks more: the kernel reads them in groups)
+  TRY(alloc_n(c, &c->lmask, (int64_t)tiles.size() * kTS * kTileClasses + 8, "lane masks"));
   TRY(alloc_n(c, &c->slot, std::max<int64_t>(N, 1), "node slots"));
   if (N) HIPCHK(c, hipMemcpyAsync(c->slot, slot_h.data(), sizeof(int32_t) * N, hipMemcpyHostToDevice, s));
   if (c->n_tiles)
     HIPCHK(c, hipMemcpyAsync(c->tiles, tiles.data(), sizeof(int4) * tiles.size(), hipMemcpyHostToDevice, s));
   HIPCHK(c, hipMemcpyAsync(c->tgrain, rec.data(), sizeof(TileGrain) * rec.size(), hipMemcpyHostToDevice, s));
+  if (!tnorm.empty())
+    HIPCHK(c, hipMemcpyAsync(c->tnorm, tnorm.data(), sizeof(TileNorms) * tnorm.size(), hipMemcpyHostToDevice, s));
   if (!ttab.empty())
     HIPCHK(c, hipMemcpyAsync(c->ttab, ttab.data(), sizeof(StencilC) * ttab.size(), hipMemcpyHostToDevice, s));
   HIPCHK(c, hipMemcpyAsync(c->ctob, ctob.data(), sizeof(int16_t) * ctob.size(), hipMemcpyHostToDevice, s));
@@ -1013,9 +1036,8 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
     gc.V = h * h * h;
     gc.cVih = cc * gc.V / h;
     gc.conic_inv_delta = (P.flags & PD_FLAG_CONIC) ? 1.0 / delta : 0.0;
-    // break tests on |y|^2 - |xi|^2 against |xi|^2 ((1 +- s0)^2 - 1), |xi|^2 = h^2 |d|^2
-    gc.thr = h * h * s0 * (2.0 + s0);
-    gc.abs_ratio = (2.0 - s0) / (2.0 + s0);
+    gc.thr_x = s0 * (2.0 + s0);
+    gc.lo_x = -s0 * (2.0 - s0);
     gc.h = h;
     gc.rho = mt.density;
     for (int q = 0; q < 3; ++q) gc.origin[q] = grains->origin[q * G + g];
@@ -1046,7 +1068,7 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
       }
   c->n_stencil = (int32_t)(sd.size() / 3);
   c->n_classes = (int32_t)classes.size();
-  if ((int64_t)c->n_classes * (c->n_stencil + 1) * (int64_t)sizeof(StencilC) > kMaxLdsTables)
+  if ((int64_t)c->n_classes * (c->n_stencil + 1) * (int64_t)kTableRow > kMaxLdsTables)
     return fail(c, PD_ERR_UNSUPPORTED, "%d distinct (h, material) classes exceed the stencil-table space",
                 c->n_classes);
   std::vector<StencilC> st;
@@ -1061,11 +1083,10 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
       const double l0 = h * sqrt(d2), l0sq = h * h * d2;
       // micromodulus weight: 1, or 1 - |xi|/delta for the conic form
       const double w = (P.flags & PD_FLAG_CONIC) ? 1.0 - l0 / (P.horizon_factor * h) : 1.0;
-      st.push_back(StencilC{h * sd[3 * k], h * sd[3 * k + 1], h * sd[3 * k + 2], l0sq * s0 * (2.0 + s0),
-                            1.0 / l0sq, cV * w / l0, l0, l0sq});
+      st.push_back(StencilC{h * sd[3 * k], h * sd[3 * k + 1], h * sd[3 * k + 2], 1.0 / l0sq, cV * w / l0, l0, l0sq});
     }
     // zero-force class: xi = 0, x = 0, c V / |xi| = 0 (broken bonds, padding)
-    st.push_back(StencilC{0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 1.0, 1.0});
+    st.push_back(StencilC{0.0, 0.0, 0.0, 0.0, 0.0, 1.0, 1.0});
   }
   c->stencil_h = st;
   c->sd_h = sd;
@@ -1316,8 +1337,12 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
   TRY(alloc_n(c, &c->origin, 4, "cell grid origin"));
   TRY(alloc_n(c, &c->rank, N, "ranks in buckets"));
   TRY(alloc_n(c, &c->srec, N, "binned records"));
-  TRY(alloc_n(c, &c->cand_scratch, (int64_t)c->scratch_w * N, "candidate scratch rows"));
-  TRY(alloc_n(c, &c->cellh, N, "cell hashes"));
+  // the candidate scratch rows, written by the search; until the scatter has run
+  // their memory holds what the binning hands it (40 bytes a node)
+  TRY(alloc_n(c, &c->cand_scratch, std::max<int64_t>(c->scratch_w, 10) * N, "candidate scratch rows"));
+  c->rec = reinterpret_cast<int4*>(c->cand_scratch);
+  c->cellh = reinterpret_cast<uint32_t*>(c->rec + 2 * N);
+  c->rank = reinterpret_cast<int32_t*>(c->cellh + N);
   TRY(alloc_n(c, &c->grid, 8, "cell grid"));
   TRY(alloc_n(c, &c->bucket_count, (int64_t)T + 1, "bucket counts"));
   TRY(alloc_n(c, &c->bucket_start, (int64_t)T + 1, "bucket starts"));

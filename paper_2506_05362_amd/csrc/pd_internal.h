@@ -24,18 +24,16 @@ constexpr int kChunk = 1024;        // wall-partial columns reduced by one workg
 #define PD_CONTACT_BATCH 2
 #endif
 constexpr int kContactBatch = PD_CONTACT_BATCH;  // contact candidates whose gathers a lane issues together
-#ifndef PD_BOND_UNROLL
-#define PD_BOND_UNROLL 8
-#endif
-constexpr int kUnroll = PD_BOND_UNROLL;  // bond entries in flight per lane; slice widths are padded to it
+constexpr int kUnroll = 8;  // slice widths are padded to a multiple of it
+constexpr int kBatch = 4;   // bond entries whose gathers a lane issues together
 
 // per-grain constants
 struct GrainC {
   double cVih;    // c * V / h (micromodulus, or c0 of the conic form, times nodal volume, over h)
   double conic_inv_delta;  // 1/delta with the conic micromodulus c0 (1 - |xi|/delta), else 0
-  double thr;     // h^2 s0 (2 + s0): bond breaks when |y|^2 - |xi|^2 > thr * |d|^2  (s > s0)
-  double abs_ratio;  // (2 - s0) / (2 + s0): with the |s| reading a bond also breaks when
-                     // |y|^2 - |xi|^2 < -abs_ratio * thr * |d|^2  (s < -s0)
+  // a bond breaks when x = (|y|^2 - |xi|^2) / |xi|^2 > thr_x = (1 + s0)^2 - 1  (s > s0), with the
+  // |s| reading also when x < lo_x = (1 - s0)^2 - 1  (s < -s0)
+  double thr_x, lo_x;
   double h;
   double V;       // h^3
   double rho;
@@ -46,16 +44,15 @@ struct GrainC {
 
 // One row per horizon-stencil offset d (lexicographic order) and per
 // (h, material) class, with every constant of the bond law folded in:
-// xi = h d, the break threshold on |y|^2 - |xi|^2, 1/|xi|^2, c V / |xi|,
-// |xi| and |xi|^2.  The last row of each class is the zero-force class used by
-// broken bonds and padding.
+// xi = h d, 1/|xi|^2, c V / |xi|, and for the exact form |xi|, |xi|^2.  The row
+// after the last offset is the zero-force class of broken bonds and padding.
 struct StencilC {
   double hx, hy, hz;  // xi
-  double thr_d;       // |xi|^2 ((1 + s0)^2 - 1)
   double inv_l0sq;    // 1 / |xi|^2
   double civ;         // c V / |xi|
   double l0, l0sq;    // |xi|, |xi|^2
 };
+constexpr int kTableRow = 64;  // bytes of a row counted against the tables' space
 constexpr int kMaxLdsTables = 48 * 1024;  // bytes of stencil tables a workgroup may stage
 constexpr int kMaxStencil = 1024;
 constexpr int kCornerGL = 32;  // Gauss-Legendre points per piece of a wall-corner region integral
@@ -82,6 +79,17 @@ static_assert(kTM * kTF == kWave, "a wavefront holds one layer of a tile");
 constexpr int kHS = kTS + 2 * kTileR, kHM = kTM + 2 * kTileR, kHF = kTF + 2 * kTileR;
 constexpr int kHalo = kHS * kHM * kHF;      // 3080 cells, 73920 B of FP64 planes (8 layers)
 constexpr int kTileClasses = 122;           // 0 < |d|^2 <= 9
+
+// The same constants for the tile kernel, by |d|^2 (the eight sums of three
+// squares up to 9; all rows of one |d|^2 hold equal values).
+constexpr int kTileNorms = 8;
+constexpr int tile_norm(int d2) { return d2 < 7 ? d2 - 1 : d2 - 2; }  // no |d|^2 = 7
+struct TileNorms {
+  double h[4];  // 0, h, 2 h, 3 h
+  double thr_x, lo_x;
+  double bond[kTileNorms][2];  // 1 / |xi|^2, c V / |xi|
+  double l0[kTileNorms], l0sq[kTileNorms];
+};
 
 // A tile box: a grain's own lattice box, or (lattice mode) one box over every
 // grain when all of them share one lattice, spacing, bond table and node order.
@@ -190,6 +198,7 @@ struct StepArgs {
   const TileGrain* tgrain;
   const int32_t* tmap;
   const StencilC* ttab;
+  const TileNorms* tnorm;  // one per bond table
   uint64_t* lmask;        // [n_tiles * kTS][kTileClasses] lane masks of intact bonds
   const int32_t* slot;    // [n]: node -> (tile * kTS + wavefront) * 64 + lane, or -1
   // self-contact inside a grain (Sec. 5): a same-grain candidate pair is
