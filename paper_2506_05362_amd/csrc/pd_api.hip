@@ -83,6 +83,9 @@ struct pd_ctx {
   WallDev* walls = nullptr;
   double* wall_partial = nullptr;
   double* wall_chunk = nullptr;
+  uint8_t* wall_touched = nullptr;
+  int alike = 0;  // all grains share spacing and material, whose constants these are
+  GrainOne one{};
   int64_t* box_chunks = nullptr;
   int32_t n_box_chunks = 0;
   int64_t* step_d = nullptr;
@@ -338,6 +341,9 @@ StepArgs step_args(pd_ctx* c) {
   A.walls = c->walls;
   A.wall_partial = c->wall_partial;
   A.wall_chunk = c->wall_chunk;
+  A.wall_touched = c->wall_touched;
+  A.alike = c->alike;
+  A.one = c->one;
   A.step = c->step_d;
   A.advance = 1;
   A.status = c->status;
@@ -1040,6 +1046,7 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
     gc.lo_x = -s0 * (2.0 - s0);
     gc.h = h;
     gc.rho = mt.density;
+    gc.inv_rho = 1.0 / mt.density;
     for (int q = 0; q < 3; ++q) gc.origin[q] = grains->origin[q * G + g];
     gc.mat = grains->material[g];
     const std::pair<double, int32_t> key(h, gc.mat);
@@ -1054,6 +1061,11 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
       const double keff = 2.0 * ka * kb / (ka + kb);
       kn[(size_t)a * n_mat + b] = 18.0 * keff / (kPi * pow(P.contact_horizon, 5));
     }
+  {
+    const GrainC& g0 = c->grains_h[0];
+    c->alike = classes.size() == 1 ? 1 : 0;
+    c->one = GrainOne{g0.h, g0.V, g0.rho, g0.inv_rho, kn[(size_t)g0.mat * n_mat + g0.mat]};
+  }
   // horizon stencil 0 < |d|^2 <= m^2 in lexicographic order; its index rides in
   // the top bits of every column word
   std::vector<int> sd;
@@ -1395,6 +1407,7 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
   TRY(build_tiles(c));
   c->partial_cols = std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(c->nslices, c->pg_cols), kTS * c->n_tiles), 1);
   TRY(alloc_n(c, &c->wall_partial, c->partial_cols * 3 * std::max(c->n_walls, 1), "wall partials"));
+  TRY(alloc_n(c, &c->wall_touched, c->partial_cols, "walls touched"));
   TRY(alloc_n(c, &c->wall_chunk, ((c->partial_cols + kChunk - 1) / kChunk) * 3 * std::max(c->n_walls, 1),
               "wall chunk sums"));
 

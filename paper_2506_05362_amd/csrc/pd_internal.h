@@ -36,10 +36,15 @@ struct GrainC {
   double thr_x, lo_x;
   double h;
   double V;       // h^3
-  double rho;
+  double rho, inv_rho;
   double origin[3];
   int32_t mat;
   int32_t cls;    // index of the (h, material) stencil table
+};
+
+// a grain's constants in the node tail
+struct GrainOne {
+  double h, V, rho, inv_rho, Kn;  // Kn between two nodes of its material
 };
 
 // One row per horizon-stencil offset d (lexicographic order) and per
@@ -163,8 +168,11 @@ struct StepArgs {
   const double* X;      // SoA, contact path only
   const double4* X4;    // the same as (x, y, z, 0) per node: one load per contact candidate
   const double* Kn;     // [n_mat * n_mat]
+  int32_t alike;        // every grain has the same spacing and material: their constants are in `one`
+  GrainOne one;
   WallDev* walls;
   double* wall_partial;  // [n_walls][3][partial_stride]: one column per slice (component-major)
+  uint8_t* wall_touched; // [partial_stride] bit w: this column's slice touched wall w (its partials are set)
   double* wall_chunk;    // [n_walls][3][chunks]: sums of 1024-column chunks of wall_partial
   int64_t* step;         // device step counter
   int32_t advance;       // 1 when this evaluation completes a step, 0 for the initial one
