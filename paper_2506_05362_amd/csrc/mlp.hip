@@ -41,14 +41,7 @@ __device__ __forceinline__ v4f mfma_16x16x32(const v8s& a, const v8s& b, const v
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
-// FP32 -> BF16, round to nearest even (NaN kept quiet)
-__device__ __forceinline__ short to_bf16(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (short)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (short)(u >> 16);
-}
-
+// FP32 -> BF16, round to nearest even (the conversion instruction)
 __device__ __forceinline__ v8s to_bf16x8(const v8f& x) {
   return __builtin_bit_cast(v8s, __builtin_convertvector(x, v8bf));
 }
@@ -425,197 +418,152 @@ __global__ void k_adam(float* p, const float* g, float* m, float* v, int64_t n, 
 }
 
 // ---------------------------------------------------------------------------
-// Fused inference for din <= 16 -> 256 -> 256 -> 256 -> dout <= 16.
-// Phase A: layer 1 on the vector units (its 6-wide products are too small for
-// the matrix cores), its GELU outputs become the BF16 A operand of layer 2
-// directly in registers; layer 2 on the matrix cores with W2 resident in LDS;
-// GELU; BF16 H2 to HBM.  Phase B: layer 3 from H2 with W3 in LDS; each 16 x 16
-// output tile is GELU'd and turned into the A operand of layer 4 through a
-// small per-wavefront LDS tile, so layer 4 runs on the matrix cores as it goes.
-// Operands are rounded to BF16 exactly where the layer-by-layer path rounds
-// them (x, W1, activations, W2..W4); accumulation is FP32.
-// Each workgroup keeps a weight matrix in LDS and walks tiles of 16 rows per
-// wavefront.  The weights fill most of a CU's LDS, so one workgroup runs per
-// CU: eight wavefronts (two per SIMD) let one hide the latency of the other's
-// vector work (the exact-erf GELUs) and matrix-core chains.
+// Fused inference for din <= 16 -> 256 -> 256 -> 256 -> dout <= 16, one launch.
+// A workgroup of eight wavefronts keeps W2 and W3 in registers (wavefront w the
+// 32 columns from 32 w, as matrix-core operands: 128 VGPRs) and walks tiles of
+// 16 R rows.  Layer 1 runs on the vector units (its 6-wide products are too small
+// for the matrix cores), a wavefront computing its 32 hidden units; activations
+// pass between the layers through LDS in BF16, one barrier each; layer 4 is one
+// wavefront's work per 16 rows.  Weights take the matrix cores' A side, so that a
+// lane ends up with four neighbouring units of one row: one 8-byte LDS store.
+// Operands are rounded to BF16 exactly where the layer-by-layer path rounds them
+// (x, W1, activations, W2..W4) and every sum runs in its order; accumulation is
+// FP32.
+//
+// Bound by the vector units: 768 exact-erf GELUs a row, some 44 instructions each.
+// 1e7 rows: 8.0 ms (as two kernels with the weights in LDS, the second hidden
+// layer's activations stored between them and 2-byte stores: 12.9 ms); 100 rows,
+// which those two kernels put on one CU: 30 us a call instead of 71.
 // ---------------------------------------------------------------------------
 
 constexpr int kH = 256;          // hidden width of the fused path
-constexpr int kWRow = kH + 8;    // LDS row of a transposed weight matrix (bf16), padded, 16-byte aligned
-constexpr int kTRow = 32 + 8;    // per-wavefront transpose tile row (bf16)
-constexpr int kIW = 8;           // wavefronts per workgroup
-constexpr int kIRows = 16 * kIW;  // batch rows per tile
+constexpr int kHRow = kH + 8;    // LDS row of activations (bf16), 16-byte aligned, banks staggered
+constexpr int kIW = 8;           // wavefronts per workgroup, 32 hidden units each
 
-// Order the LDS accesses of one wavefront's lanes (all of them converged here):
-// writes before the call are seen by reads after it in every lane.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ float bf16_to_f(short h) { return __uint_as_float(((uint32_t)(uint16_t)h) << 16); }
+__device__ __forceinline__ float round_bf16(float x) { return (float)(__bf16)x; }
 
 struct Infer {
   const float* x;
   int64_t M;
   int din, dout;
-  const float* W1;   // [din][kH] fp32 (rounded to bf16 on use)
-  const float* b1;
-  const short* W2t;  // [kH][kH] bf16, transposed (n-major)
-  const float* b2;
-  const short* W3t;
-  const float* b3;
-  const short* W4t;  // [16][kH] bf16, rows >= dout zero
-  const float* b4;
-  short* H2;         // [M][kH] bf16
-  float* y;          // [M][dout]
+  const float *W1, *b1, *W2, *b2, *W3, *b3, *W4, *b4;  // fp32, W [fan_in][fan_out]
+  float* y;  // [M][dout]
 };
 
-// out[n][k] = bf16(W[k][n]) for n < N, zero rows for N <= n < rows_out
-__global__ void k_pack_t(const float* W, int K, int N, int rows_out, short* out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)rows_out * K) return;
-  const int n = (int)(i / K), k = (int)(i % K);
-  out[i] = n < N ? to_bf16(W[(int64_t)k * N + n]) : (short)0;
-}
-
-__device__ __forceinline__ void stage_weights_t(const short* src, int rows, short* dst) {
-  // rows x kH bf16 (16-byte pieces) into LDS rows of kWRow
-  for (int i = threadIdx.x; i < rows * (kH / 8); i += blockDim.x) {
-    const int r = i / (kH / 8), c = (i % (kH / 8)) * 8;
-    *reinterpret_cast<v8s*>(dst + r * kWRow + c) = *reinterpret_cast<const v8s*>(src + (int64_t)r * kH + c);
+// operand of the 16 units from n0 for all k: lane l holds unit n0 + l % 16, k = 32
+// kk + 8 (l / 16) + j
+__device__ __forceinline__ void load_units(const float* W, int n0, v8s (&f)[kH / 32]) {
+  const int lane = threadIdx.x & 63;
+  const float* p = W + (int64_t)8 * (lane >> 4) * kH + n0 + (lane & 15);
+#pragma unroll
+  for (int kk = 0; kk < kH / 32; ++kk) {
+    v8f v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = p[(kk * 32 + j) * kH];
+    f[kk] = to_bf16x8(v);
   }
 }
 
-template <int DINP>
-__global__ __launch_bounds__(64 * kIW) void k_infer_a(Infer a) {
-  extern __shared__ __align__(16) char smem[];
-  short* sW = reinterpret_cast<short*>(smem);                                   // [kH][kWRow]
-  float* sW1 = reinterpret_cast<float*>(smem + sizeof(short) * kH * kWRow);     // [DINP][kH]
-  float* sb1 = sW1 + DINP * kH;
-  float* sb2 = sb1 + kH;
-  short* sT = reinterpret_cast<short*>(sb2 + kH);                               // [kIW][16][kTRow]
-  const int tid = threadIdx.x;
-  stage_weights_t(a.W2t, kH, sW);
-  for (int i = tid; i < DINP * kH; i += blockDim.x) sW1[i] = i < a.din * kH ? bf16_to_f(to_bf16(a.W1[i])) : 0.0f;
-  for (int i = tid; i < kH; i += blockDim.x) {
-    sb1[i] = a.b1[i];
-    sb2[i] = a.b2[i];
+// one hidden layer of the wavefront's 32 units: GELU(W^T act + b) into out
+template <int R>
+__device__ __forceinline__ void hidden(const v8s (&w)[2][kH / 32], const float* bias, int n0,
+                                       const short (*in)[kHRow], short (*out)[kHRow]) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+  v4f acc[R][2];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r][0] = acc[r][1] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kk = 0; kk < kH / 32; ++kk)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const v8s act = *reinterpret_cast<const v8s*>(&in[16 * r + lr][kk * 32 + 8 * lg]);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) acc[r][c] = mfma_16x16x32(w[c][kk], act, acc[r][c]);
+    }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int n = n0 + 16 * c + 4 * lg;  // the lane's four units
+    const v4f b = *reinterpret_cast<const v4f*>(bias + n);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      v4f g;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[e] = gelu(acc[r][c][e] + b[e]);
+      *reinterpret_cast<v4s*>(&out[16 * r + lr][n]) = to_bf16x4(g);
+    }
+  }
+}
+
+template <int DINP, int R>
+__global__ __launch_bounds__(64 * kIW) void k_infer(Infer a) {
+  __shared__ __align__(16) short act[3][16 * R][kHRow];
+  __shared__ __align__(16) short sW4[16][kHRow];   // transposed, units >= dout zero
+  __shared__ __align__(16) float sW1[DINP][kH];
+  __shared__ __align__(16) float sb[3][kH];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), n0 = 32 * wv;
+  v8s w2[2][kH / 32], w3[2][kH / 32];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) load_units(a.W2, n0 + 16 * c, w2[c]);
+  for (int i = tid; i < DINP * kH; i += 64 * kIW) (&sW1[0][0])[i] = i < a.din * kH ? round_bf16(a.W1[i]) : 0.0f;
+  for (int i = tid; i < kH; i += 64 * kIW) {
+    sb[0][i] = a.b1[i];
+    sb[1][i] = a.b2[i];
+    sb[2][i] = a.b3[i];
+  }
+  for (int i = tid; i < 16 * kH; i += 64 * kIW) {
+    const int k = i / 16, n = i % 16;
+    sW4[n][k] = __builtin_bit_cast(short, (__bf16)(n < a.dout ? a.W4[(int64_t)k * a.dout + n] : 0.0f));
   }
   __syncthreads();
-  const int wv = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
-  short* T = sT + wv * 16 * kTRow;
-  const int64_t ntiles = (a.M + kIRows - 1) / kIRows;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) load_units(a.W3, n0 + 16 * c, w3[c]);
+  const int64_t ntiles = (a.M + 16 * R - 1) / (16 * R);
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int64_t r0 = t * kIRows + wv * 16;
-    const int64_t row = r0 + lr;
-    float xv[DINP];
+    // layer 1: the lane's row lr of each 16, hidden units n0 + 8 lg + 0..7
 #pragma unroll
-    for (int i = 0; i < DINP; ++i) xv[i] = (i < a.din && row < a.M) ? bf16_to_f(to_bf16(a.x[row * a.din + i])) : 0.0f;
-    // k-step outer: the layer-1 output for this k-step is the A operand of all
-    // 16 output tiles of layer 2, each with its own accumulator
-    v4f acc[16];
+    for (int r = 0; r < R; ++r) {
+      const int64_t row = t * 16 * R + 16 * r + lr;
+      float xv[DINP];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-    for (int kk = 0; kk < kH / 32; ++kk) {
-      v8s A;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = kk * 32 + 8 * lg + j;
-        float z = 0.0f;
-#pragma unroll
-        for (int i = 0; i < DINP; ++i) z = fmaf(xv[i], sW1[i * kH + k], z);
-        A[j] = to_bf16(gelu(z + sb1[k]));
+      for (int i = 0; i < DINP; ++i) {
+        const float v = a.x[(row < a.M ? row : a.M - 1) * a.din + (i < a.din ? i : 0)];
+        xv[i] = i < a.din ? round_bf16(v) : 0.0f;
       }
+      float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const v8s b = *reinterpret_cast<const v8s*>(sW + (q * 16 + lr) * kWRow + kk * 32 + 8 * lg);
-        acc[q] = mfma_16x16x32(A, b, acc[q]);
+      for (int i = 0; i < DINP; ++i) {
+        const v8f w = *reinterpret_cast<const v8f*>(&sW1[i][n0 + 8 * lg]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) z[j] = fmaf(xv[i], w[j], z[j]);
       }
+      const v8f b = *reinterpret_cast<const v8f*>(&sb[0][n0 + 8 * lg]);
+      v8f g;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) g[j] = gelu(z[j] + b[j]);
+      *reinterpret_cast<v8s*>(&act[0][16 * r + lr][n0 + 8 * lg]) = to_bf16x8(g);
     }
-    // GELU of each pair of 16 x 16 tiles through this wavefront's LDS tile,
-    // so that every lane stores 16 contiguous bytes of one row of H2
+    __syncthreads();
+    hidden<R>(w2, sb[1], n0, act[0], act[1]);
+    __syncthreads();
+    hidden<R>(w3, sb[2], n0, act[1], act[2]);
+    __syncthreads();
+    // layer 4 (the next tile's first write to act[2] is two barriers away)
+    if (wv < R) {
+      v4f o = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q2 = 0; q2 < 8; ++q2) {
+      for (int kk = 0; kk < kH / 32; ++kk)
+        o = mfma_16x16x32(*reinterpret_cast<const v8s*>(&sW4[lr][kk * 32 + 8 * lg]),
+                          *reinterpret_cast<const v8s*>(&act[2][16 * wv + lr][kk * 32 + 8 * lg]), o);
+      const int64_t row = t * 16 * R + 16 * wv + lr;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int q = 2 * q2 + h, col = q * 16 + lr;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) T[(4 * lg + e) * kTRow + 16 * h + lr] = to_bf16(gelu(acc[q][e] + sb2[col]));
+      for (int e = 0; e < 4; ++e) {
+        const int n = 4 * lg + e;
+        if (row < a.M && n < a.dout) a.y[row * a.dout + n] = o[e] + a.b4[n];
       }
-      wave_sync();
-      const v8s hv = *reinterpret_cast<const v8s*>(T + lr * kTRow + 8 * lg);
-      if (row < a.M) *reinterpret_cast<v8s*>(a.H2 + row * kH + q2 * 32 + 8 * lg) = hv;
-      wave_sync();
     }
   }
 }
-
-__global__ __launch_bounds__(64 * kIW) void k_infer_b(Infer a) {
-  extern __shared__ __align__(16) char smem[];
-  short* sW = reinterpret_cast<short*>(smem);                  // [kH][kWRow]
-  short* sW4 = sW + kH * kWRow;                                // [16][kWRow]
-  short* sT = sW4 + 16 * kWRow;                                // [kIW][16][kTRow]
-  static_assert((kWRow * 2) % 16 == 0 && (kTRow * 2) % 16 == 0, "16-byte LDS rows");
-  float* sb3 = reinterpret_cast<float*>(sT + kIW * 16 * kTRow);  // [kH]
-  float* sb4 = sb3 + kH;                                       // [16]
-  const int tid = threadIdx.x;
-  stage_weights_t(a.W3t, kH, sW);
-  stage_weights_t(a.W4t, 16, sW4);
-  for (int i = tid; i < kH; i += blockDim.x) sb3[i] = a.b3[i];
-  if (tid < 16) sb4[tid] = tid < a.dout ? a.b4[tid] : 0.0f;
-  __syncthreads();
-  const int wv = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
-  short* T = sT + wv * 16 * kTRow;
-  const int64_t ntiles = (a.M + kIRows - 1) / kIRows;
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int64_t r0 = t * kIRows + wv * 16;
-    const int64_t row = r0 + lr;
-    v4f acc[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-    for (int kk = 0; kk < kH / 32; ++kk) {
-      const v8s A = row < a.M ? *reinterpret_cast<const v8s*>(a.H2 + row * kH + kk * 32 + 8 * lg)
-                              : v8s{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const v8s b = *reinterpret_cast<const v8s*>(sW + (q * 16 + lr) * kWRow + kk * 32 + 8 * lg);
-        acc[q] = mfma_16x16x32(A, b, acc[q]);
-      }
-    }
-    // each pair of 16 x 16 tiles of layer 3: GELU, then transposed into the
-    // 16 x 32 A operand of layer 4
-    v4f acc4 = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q2 = 0; q2 < 8; ++q2) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int q = 2 * q2 + h, col = q * 16 + lr;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) T[(4 * lg + e) * kTRow + 16 * h + lr] = to_bf16(gelu(acc[q][e] + sb3[col]));
-      }
-      wave_sync();  // T is this wavefront's own tile: no wait for the others
-      const v8s a4 = *reinterpret_cast<const v8s*>(T + lr * kTRow + 8 * lg);
-      const v8s b4 = *reinterpret_cast<const v8s*>(sW4 + lr * kWRow + q2 * 32 + 8 * lg);
-      acc4 = mfma_16x16x32(a4, b4, acc4);
-      wave_sync();
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t rr = r0 + 4 * lg + e;
-      if (rr < a.M && lr < a.dout) a.y[rr * a.dout + lr] = acc4[e] + sb4[lr];
-    }
-  }
-}
-
-template <int DINP>
-constexpr size_t lds_a() {
-  return sizeof(short) * (kH * kWRow + kIW * 16 * kTRow) + sizeof(float) * (DINP * kH + 2 * kH);
-}
-constexpr size_t kLdsB = sizeof(short) * (kH * kWRow + 16 * kWRow + kIW * 16 * kTRow) + sizeof(float) * (kH + 16);
 
 }  // namespace
 
@@ -635,7 +583,6 @@ struct pdm_net {
   float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f, weight_decay = 0.0f;
   // fused inference path (din <= 16 -> 256 -> 256 -> 256 -> dout <= 16)
   int fused_ok = 0, use_fused = 0, cus = 0;
-  short *W2t = nullptr, *W3t = nullptr, *W4t = nullptr, *H2 = nullptr;
   int64_t t = 0;
   std::vector<void*> owned;
   pd_alloc_fn alloc = nullptr;  // caller's device allocator (hipMalloc when none)
@@ -861,22 +808,10 @@ pd_status pdm_create(pdm_net** out, const int32_t* dims, int32_t n_dims, int64_t
   TRY(alloc(n, &n->xrows, max_batch * row4(dims[0])));
   if (n_dims == 5 && dims[1] == kH && dims[2] == kH && dims[3] == kH && dims[0] <= 16 && dims[4] <= 16) {
     int dev = 0, lds = 0;
-    const size_t need_a = dims[0] <= 8 ? lds_a<8>() : lds_a<16>();
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
-        hipDeviceGetAttribute(&n->cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        (size_t)lds >= need_a && (size_t)lds >= kLdsB &&
-        hipFuncSetAttribute(dims[0] <= 8 ? reinterpret_cast<const void*>(&k_infer_a<8>)
-                                         : reinterpret_cast<const void*>(&k_infer_a<16>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)need_a) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_infer_b),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsB) == hipSuccess) {
-      TRY(alloc(n, &n->W2t, (int64_t)kH * kH));
-      TRY(alloc(n, &n->W3t, (int64_t)kH * kH));
-      TRY(alloc(n, &n->W4t, (int64_t)16 * kH));
-      TRY(alloc(n, &n->H2, max_batch * kH));
+        hipDeviceGetAttribute(&n->cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && lds >= 160 * 1024)
       n->fused_ok = n->use_fused = 1;
-    }
     (void)hipGetLastError();
   }
   n->nloss_blocks = 256;
@@ -933,39 +868,33 @@ pd_status pdm_forward(pdm_net* n, const float* x, int64_t batch, float* y) {
   if (!n || (!x && batch > 0) || (!y && batch > 0) || batch < 0) return PD_ERR_INVALID;
   const int64_t din = n->dims.front(), dout = n->dims.back();
   if (n->use_fused && batch > 0) {
-    // BF16 transposed copies of W2, W3, W4 (parameters may have changed since the last call)
-    const int64_t e = (int64_t)kH * kH;
-    hipLaunchKernelGGL(k_pack_t, dim3((unsigned)((e + 255) / 256)), dim3(256), 0, n->stream,
-                       n->params + n->woff[1], kH, kH, kH, n->W2t);
-    hipLaunchKernelGGL(k_pack_t, dim3((unsigned)((e + 255) / 256)), dim3(256), 0, n->stream,
-                       n->params + n->woff[2], kH, kH, kH, n->W3t);
-    hipLaunchKernelGGL(k_pack_t, dim3((unsigned)((16 * kH + 255) / 256)), dim3(256), 0, n->stream,
-                       n->params + n->woff[3], kH, (int)dout, 16, n->W4t);
-    HIPCHK(n, hipGetLastError());
-    for (int64_t b0 = 0; b0 < batch; b0 += n->max_batch) {
-      const int64_t cb = batch - b0 < n->max_batch ? batch - b0 : n->max_batch;
-      Infer a{};
-      a.x = x + b0 * din;
-      a.M = cb;
-      a.din = (int)din;
-      a.dout = (int)dout;
-      a.W1 = n->params + n->woff[0];
-      a.b1 = n->params + n->boff[0];
-      a.W2t = n->W2t;
-      a.b2 = n->params + n->boff[1];
-      a.W3t = n->W3t;
-      a.b3 = n->params + n->boff[2];
-      a.W4t = n->W4t;
-      a.b4 = n->params + n->boff[3];
-      a.H2 = n->H2;
-      a.y = y + b0 * dout;
-      const int64_t tiles = (cb + kIRows - 1) / kIRows;
-      const unsigned grid = (unsigned)std::min<int64_t>(tiles, std::max(n->cus, 1));
-      if (din <= 8) hipLaunchKernelGGL(k_infer_a<8>, dim3(grid), dim3(64 * kIW), lds_a<8>(), n->stream, a);
-      else hipLaunchKernelGGL(k_infer_a<16>, dim3(grid), dim3(64 * kIW), lds_a<16>(), n->stream, a);
-      hipLaunchKernelGGL(k_infer_b, dim3(grid), dim3(64 * kIW), kLdsB, n->stream, a);
-      HIPCHK(n, hipGetLastError());
+    Infer a{};
+    a.x = x;
+    a.M = batch;
+    a.din = (int)din;
+    a.dout = (int)dout;
+    a.W1 = n->params + n->woff[0];
+    a.b1 = n->params + n->boff[0];
+    a.W2 = n->params + n->woff[1];
+    a.b2 = n->params + n->boff[1];
+    a.W3 = n->params + n->woff[2];
+    a.b3 = n->params + n->boff[2];
+    a.W4 = n->params + n->woff[3];
+    a.b4 = n->params + n->boff[3];
+    a.y = y;
+    // 32 rows a tile once they give every CU a workgroup, one workgroup a CU
+    const int64_t cus = std::max(n->cus, 1);
+    const bool wide = batch > 32 * cus;
+    const int64_t tiles = wide ? (batch + 31) / 32 : (batch + 15) / 16;
+    const dim3 grid((unsigned)std::min<int64_t>(tiles, wide ? cus : 2 * cus)), block(64 * kIW);
+    if (din <= 8) {
+      if (wide) hipLaunchKernelGGL((k_infer<8, 2>), grid, block, 0, n->stream, a);
+      else hipLaunchKernelGGL((k_infer<8, 1>), grid, block, 0, n->stream, a);
+    } else {
+      if (wide) hipLaunchKernelGGL((k_infer<16, 2>), grid, block, 0, n->stream, a);
+      else hipLaunchKernelGGL((k_infer<16, 1>), grid, block, 0, n->stream, a);
     }
+    HIPCHK(n, hipGetLastError());
   } else {
     for (int64_t b0 = 0; b0 < batch; b0 += n->max_batch) {
       const int64_t cb = batch - b0 < n->max_batch ? batch - b0 : n->max_batch;
