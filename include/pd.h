@@ -233,7 +233,9 @@ pd_status pd_step(pd_ctx* ctx, int64_t n_steps);
 pd_status pd_field_bytes(pd_ctx* ctx, pd_field field, int64_t* bytes);
 
 /* Copy a field into dst (host memory, or device memory when dst_on_device != 0).
-   dst_bytes smaller than the field gives PD_ERR_INVALID.  Synchronises the stream. */
+   dst_bytes smaller than the field gives PD_ERR_INVALID.  Synchronises the stream.
+   Device memory is written on the context's stream: what other streams do with it
+   has to be done by then. */
 pd_status pd_get(pd_ctx* ctx, pd_field field, void* dst, int64_t dst_bytes, int32_t dst_on_device);
 
 /* The four energies of PD_ENERGY (kinetic, elastic, contact, gravity potential

@@ -324,6 +324,10 @@ class Sim:
         return out
 
     def get_device(self, name: str, dst_ptr: int, nbytes: int):
+        """pd_get into device memory, after whatever the caller's current stream still does with it."""
+        torch = sys.modules.get("torch")
+        if torch is not None and torch.cuda.is_initialized() and not torch.cuda.is_current_stream_capturing():
+            torch.cuda.current_stream().synchronize()
         self._check(lib().pd_get(self.h, FIELDS[name], P(dst_ptr), nbytes, 1))
 
     def info(self) -> dict:
