@@ -71,6 +71,9 @@ struct pd_ctx {
   std::vector<void*> owned;
   // device state
   double4* u4[2] = {nullptr, nullptr};
+  // u of u4 as (x, y) and z, next to lined: its steps read and write it with u4
+  double2* uxy[2] = {nullptr, nullptr};
+  double* uz[2] = {nullptr, nullptr};
   double4* vh[2] = {nullptr, nullptr};  // mid-step velocities, indexed like u4 (beta or mu > 0)
   double *v = nullptr, *a = nullptr, *X = nullptr, *F = nullptr;
   double4* X4 = nullptr;
@@ -97,6 +100,12 @@ struct pd_ctx {
   int64_t* slice_off = nullptr;
   uint32_t* colE = nullptr;
   uint32_t* colOrig = nullptr;
+  // the step's own rows on the slice path (null: it reads colE, which follows their bond memory)
+  uint32_t* lined = nullptr;
+  int64_t* lined_off = nullptr;
+  int32_t* lined_row = nullptr;
+  std::vector<int> axis_order;  // per grain, -1 in no lattice order
+  int32_t *axis_order_d = nullptr, *axis_rank = nullptr;
   int32_t* intact = nullptr;
   // contact
   uint32_t T = 0;
@@ -299,6 +308,10 @@ StepArgs step_args(pd_ctx* c) {
   StepArgs A{};
   A.ucur = c->u4[c->cur];
   A.unext = c->u4[c->cur ^ 1];
+  A.uxy = c->uxy[c->cur];
+  A.uz = c->uz[c->cur];
+  A.uxy_next = c->uxy[c->cur ^ 1];
+  A.uz_next = c->uz[c->cur ^ 1];
   A.v = c->v;
   A.a = c->a;
   A.Fout = c->F;
@@ -322,6 +335,9 @@ StepArgs step_args(pd_ctx* c) {
   A.slice_off = c->slice_off;
   A.rowlen = c->rowlen;
   A.colE = c->colE;
+  A.lined = c->lined;
+  A.lined_off = c->lined_off;
+  A.lined_row = c->lined_row;
   A.sentinel_hi = c->sentinel_hi;
   A.intact = c->intact;
   A.self_contact = (c->flags & PD_FLAG_SELF_CONTACT) ? 1 : 0;
@@ -629,6 +645,54 @@ constexpr int kAxisOrders[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {
 // (lattice mode): a dense aggregate then fills its tiles, and bonds, which
 // never join two grains, are told apart by the class masks.  Leaves tile_ok = 0
 // when some grain has no such order or the horizon factor is not 3.
+// the axis order in which a grain lists its nodes lexicographically, -1 if in none
+int lattice_order(const pd_ctx* c, int32_t g) {
+  const int64_t N = c->n, b = c->grain_begin[(size_t)g], e = c->grain_begin[(size_t)g + 1];
+  for (int p = 0; p < 6; ++p) {
+    const int* P = kAxisOrders[p];
+    bool ok = true;
+    int64_t prev = -1;
+    for (int64_t i = b; i < e && ok; ++i) {
+      const int64_t key = ((int64_t)c->ijk_h[P[0] * N + i] << 20) | ((int64_t)c->ijk_h[P[1] * N + i] << 10) |
+                          (int64_t)c->ijk_h[P[2] * N + i];
+      ok = key > prev;
+      prev = key;
+    }
+    if (ok) return p;
+  }
+  return -1;
+}
+
+// axis_order, and on the device the place of every horizon class in rows of each order
+// (stencil: the offsets, packed and lexicographic)
+pd_status rank_classes(pd_ctx* c, const std::vector<int32_t>& stencil) {
+  c->axis_order.resize((size_t)c->n_grains);
+  std::vector<int32_t> order((size_t)c->n_grains);
+  for (int32_t g = 0; g < c->n_grains; ++g) {
+    c->axis_order[(size_t)g] = lattice_order(c, g);
+    order[(size_t)g] = std::max(c->axis_order[(size_t)g], 0);
+  }
+  const size_t ns = stencil.size();
+  std::vector<int32_t> rank(6 * ns);
+  for (int p = 0; p < 6; ++p) {
+    std::vector<std::pair<int32_t, int32_t>> by(ns);
+    for (size_t k = 0; k < ns; ++k) {
+      const int32_t* P = kAxisOrders[p];
+      auto at = [&](int q) { return (stencil[k] >> (8 * P[q])) & 255; };
+      by[k] = {(at(0) << 16) | (at(1) << 8) | at(2), (int32_t)k};
+    }
+    std::sort(by.begin(), by.end());
+    for (size_t k = 0; k < ns; ++k) rank[(size_t)p * ns + (size_t)by[k].second] = (int32_t)k;
+  }
+  TRY(alloc_n(c, &c->axis_order_d, c->n_grains, "axis orders"));
+  TRY(alloc_n(c, &c->axis_rank, (int64_t)rank.size(), "class ranks"));
+  hipStream_t s = c->stream;
+  HIPCHK(c, hipMemcpyAsync(c->axis_order_d, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice, s));
+  HIPCHK(c, hipMemcpyAsync(c->axis_rank, rank.data(), sizeof(int32_t) * rank.size(), hipMemcpyHostToDevice, s));
+  HIPCHK(c, hipStreamSynchronize(s));
+  return PD_OK;
+}
+
 pd_status build_tiles(pd_ctx* c) {
   c->tile_ok = 0;
   c->tile_lattice = 0;
@@ -649,19 +713,7 @@ pd_status build_tiles(pd_ctx* c) {
   std::vector<std::array<int, 3>> glo((size_t)G), ghi((size_t)G);
   for (int32_t g = 0; g < G; ++g) {
     const int64_t b = c->grain_begin[(size_t)g], e = c->grain_begin[(size_t)g + 1];
-    int perm = -1;
-    for (int p = 0; p < 6 && perm < 0; ++p) {
-      const int* P = kAxisOrders[p];
-      bool ok = true;
-      int64_t prev = -1;
-      for (int64_t i = b; i < e && ok; ++i) {
-        const int64_t key = ((int64_t)c->ijk_h[P[0] * N + i] << 20) | ((int64_t)c->ijk_h[P[1] * N + i] << 10) |
-                            (int64_t)c->ijk_h[P[2] * N + i];
-        ok = key > prev;
-        prev = key;
-      }
-      if (ok) perm = p;
-    }
+    const int perm = c->axis_order[(size_t)g];
     if (perm < 0) return PD_OK;  // this grain's node order is not a lattice order
     int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {0, 0, 0};
     for (int64_t i = b; i < e; ++i)
@@ -885,6 +937,82 @@ pd_status build_tiles(pd_ctx* c) {
   c->tile_ok = 1;
   c->tile_lattice = lattice ? 1 : 0;
   return PD_OK;
+}
+
+AlignArgs align_args(pd_ctx* c) {
+  AlignArgs a{};
+  a.u = c->u4[0];
+  a.grains = c->grains;
+  a.rowlen = c->rowlen;
+  a.slice_off = c->slice_off;
+  a.colE = c->colE;
+  a.colOrig = c->colOrig;
+  a.off = c->lined_off;
+  a.lined = c->lined;
+  a.row = c->lined_row;
+  a.axis_order = c->axis_order_d;
+  a.axis_rank = c->axis_rank;
+  a.n = c->n;
+  a.nslices = c->nslices;
+  a.n_stencil = c->n_stencil;
+  a.node_bits = c->node_bits;
+  return a;
+}
+
+void drop_lined(pd_ctx* c) {
+  dev_free(c, c->lined);
+  dev_free(c, c->lined_off);
+  dev_free(c, c->lined_row);
+  for (int b = 0; b < 2; ++b) {
+    dev_free(c, c->uxy[b]);
+    dev_free(c, c->uz[b]);
+    c->uxy[b] = nullptr;
+    c->uz[b] = nullptr;
+  }
+  c->lined = nullptr;
+  c->lined_off = nullptr;
+  c->lined_row = nullptr;
+}
+
+// what the lined rows and the split copy of u hold, from colE, colOrig and u4
+pd_status fill_lined(pd_ctx* c) {
+  HIPCHK(c, launch_align_fill(align_args(c), c->stream));
+  for (int b = 0; b < 2; ++b) HIPCHK(c, launch_split_u(c->u4[b], c->uxy[b], c->uz[b], c->n, c->stream));
+  return PD_OK;
+}
+
+// Does this launch step over lined rows?  (The persistent kernel holds the compact
+// rows' loop only.)
+bool lines_rows(const pd_launch& l) { return l.bond_path == PD_BONDS_SLICES && l.loop != PD_LOOP_PERSISTENT; }
+
+// The lined rows and the split copy of u, for meshes that gain by them.  Without the
+// memory for them (about as much as colE takes), or with no slice that lines up, the
+// steps read colE alone.
+pd_status make_lined(pd_ctx* c) {
+  drop_lined(c);
+  if (c->nslices < kLinedSlices || c->n > kLinedNodes) return PD_OK;
+  hipStream_t s = c->stream;
+  auto get = [&](auto** p, int64_t n) {
+    *p = static_cast<std::remove_pointer_t<decltype(p)>>(dev_alloc(c, sizeof(**p) * (size_t)n));
+    return *p != nullptr;
+  };
+  int64_t *scratch = nullptr, words = 0;
+  bool ok = get(&c->lined_off, c->nslices + 1) && get(&scratch, scan_scratch_elems(c->nslices));
+  if (ok) {
+    HIPCHK(c, launch_align_width(align_args(c), s));
+    HIPCHK(c, scan_i64(c->lined_off, c->lined_off, c->nslices, scratch, s));
+    HIPCHK(c, hipMemcpyAsync(&words, c->lined_off + c->nslices, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+    ok = words > 0 && get(&c->lined, words) && get(&c->lined_row, words / kWave);
+    for (int b = 0; b < 2; ++b) ok = ok && get(&c->uxy[b], c->n) && get(&c->uz[b], c->n);
+  }
+  dev_free(c, scratch);
+  if (!ok) {
+    (void)hipGetLastError();  // of an allocation
+    drop_lined(c);
+    return PD_OK;
+  }
+  return fill_lined(c);
 }
 
 // the tile path keeps the bond memory in class masks; bring the column words
@@ -1404,6 +1532,7 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
     c->pg_part_base[(size_t)g] = c->pg_cols;
     c->pg_cols += c->pg_slice_hi[(size_t)g] - c->pg_slice_lo[(size_t)g];
   }
+  TRY(rank_classes(c, stencil));
   TRY(build_tiles(c));
   c->partial_cols = std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(c->nslices, c->pg_cols), kTS * c->n_tiles), 1);
   TRY(alloc_n(c, &c->wall_partial, c->partial_cols * 3 * std::max(c->n_walls, 1), "wall partials"));
@@ -1419,6 +1548,7 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
   HIPCHK(c, launch_wall_corners(A, 0, s));
   HIPCHK(c, launch_step(A, MODE_FIRST, s));
   HIPCHK(c, launch_wall_finalize(A, s));
+  if (lines_rows(c->launch)) TRY(make_lined(c));
   c->built = 1;
   c->step = 0;
   return report_status(c);
@@ -1504,10 +1634,13 @@ pd_status pd_set_launch(pd_ctx* c, const pd_launch* l) {
   TRY(drop_graphs(c));
   if (c->built && l->bond_path != c->launch.bond_path) {
     // hand the bond memory over: column words <-> class masks
-    StepArgs A = step_args(c);
-    if (l->bond_path == PD_BONDS_TILES) HIPCHK(c, launch_cols_to_mask(A, c->ctob, c->colOrig, c->stream));
-    else HIPCHK(c, launch_mask_to_cols(A, c->ctob, c->colOrig, c->stream));
+    if (l->bond_path == PD_BONDS_TILES) HIPCHK(c, launch_cols_to_mask(step_args(c), c->ctob, c->colOrig, c->stream));
+    else TRY(sync_columns(c));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+  }
+  if (c->built && lines_rows(*l) != lines_rows(c->launch)) {
+    if (lines_rows(*l)) TRY(make_lined(c));
+    else drop_lined(c);
   }
   c->launch = *l;
   return PD_OK;
@@ -1851,10 +1984,8 @@ pd_status pd_set_state(pd_ctx* c, const void* blob, int64_t bytes) {
     TRY(put(c->vh[c->cur], 32 * N));
     TRY(put(c->vh[c->cur ^ 1], 32 * N));
   }
-  if (c->launch.bond_path == PD_BONDS_TILES) {
-    StepArgs A = step_args(c);
-    HIPCHK(c, launch_cols_to_mask(A, c->ctob, c->colOrig, s));
-  }
+  if (c->launch.bond_path == PD_BONDS_TILES) HIPCHK(c, launch_cols_to_mask(step_args(c), c->ctob, c->colOrig, s));
+  if (c->lined) TRY(fill_lined(c));
   c->step = hdr[4];
   HIPCHK(c, hipMemcpyAsync(c->step_d, &c->step, 8, hipMemcpyHostToDevice, s));
   HIPCHK(c, hipStreamSynchronize(s));

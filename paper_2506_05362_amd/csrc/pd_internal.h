@@ -146,6 +146,11 @@ enum ForceMode { MODE_FIRST = 0, MODE_STEP = 1, MODE_FORCE_ONLY = 2 };
 struct StepArgs {
   const double4* ucur;  // (x,y,z, packed ijk | grain<<32)
   double4* unext;
+  // u again as (x, y) and z, which steps over lined rows gather and keep up
+  const double2* uxy;
+  const double* uz;
+  double2* uxy_next;
+  double* uz_next;
   double* v;            // SoA
   double* a;            // SoA
   double* Fout;         // MODE_FORCE_ONLY output (SoA)
@@ -161,6 +166,11 @@ struct StepArgs {
   const int64_t* slice_off;
   const int32_t* rowlen;
   uint32_t* colE;           // live column words; a broken bond becomes node_i | sentinel_hi
+  // the rows with classes lined up (null: the steps read colE), their slice offsets and
+  // the byte offset of each entry's row in the stencil tables
+  uint32_t* lined;
+  const int64_t* lined_off;
+  const int32_t* lined_row;
   int32_t* intact;
   const int32_t* cand_ptr;
   const int32_t* cand;
@@ -252,6 +262,30 @@ struct BuildArgs {
   int64_t nslices;
 };
 
+// rows with the classes of a slice's lanes lined up (see k_align)
+struct AlignArgs {
+  const double4* u;
+  const GrainC* grains;
+  const int32_t* rowlen;
+  const int64_t* slice_off;
+  const uint32_t* colE;
+  const uint32_t* colOrig;
+  int64_t* off;     // [nslices + 1]
+  uint32_t* lined;  // column words: node, with kBroken set where there is no bond (any more)
+  int32_t* row;     // [off[nslices] / 64]
+  int64_t n, nslices;
+  const int32_t* axis_order;  // [G] axis order of the grain's node list
+  const int32_t* axis_rank;   // [6][n_stencil] place of a class in rows of that order
+  int32_t n_stencil, node_bits;
+};
+// flags of a lined word, above any node index: no bond; one that broke in this pass
+constexpr uint32_t kBroken = 1u << 31, kFresh = 1u << 30;
+constexpr int64_t kLinedNodes = (int64_t)1 << 28;  // byte offsets of (x, y) pairs in 32 bits
+// Lined rows pay from four slices for each of 1024 SIMDs, whose wavefronts then hide each
+// other's waits for scalar loads.  Lined / compact, us a launch: 1,964 slices 48 / 42,
+// 4,190 slices 82 / 90, 8,183 slices 149 / 204, 14,139 slices 251 / 338.
+constexpr int64_t kLinedSlices = 4096;
+
 struct ContactArgs {
   const double4* u;
   const double* X;
@@ -302,6 +336,8 @@ hipError_t launch_map_fill(const BuildArgs& b, hipStream_t s);
 hipError_t launch_bond_count(const BuildArgs& b, hipStream_t s);
 hipError_t launch_slice_width(const BuildArgs& b, hipStream_t s);
 hipError_t launch_bond_fill(const BuildArgs& b, hipStream_t s);
+hipError_t launch_align_width(const AlignArgs& a, hipStream_t s);
+hipError_t launch_align_fill(const AlignArgs& a, hipStream_t s);
 hipError_t launch_step(const StepArgs& a, int mode, hipStream_t s);
 // corner corrections of this evaluation (before the step kernel)
 hipError_t launch_wall_corners(const StepArgs& a, int force_only, hipStream_t s);
@@ -335,6 +371,8 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 // fields of pd_get: u as SoA, damage 1 - intact / initial (0 where initial = 0)
 hipError_t launch_unpack_u(const double4* u4, double* out, int64_t n, hipStream_t s);
 hipError_t launch_damage(const int32_t* intact, const int32_t* initial, double* out, int64_t n, hipStream_t s);
+// the copy of u that steps over lined rows gather
+hipError_t launch_split_u(const double4* u4, double2* uxy, double* uz, int64_t n, hipStream_t s);
 // X4[i] = (X[i], X[n + i], X[2n + i], 0)
 hipError_t launch_pack_x4(const double* X, double4* X4, int64_t n, hipStream_t s);
 // tiled bond loop: MODE_STEP over all tiles (events as for launch_step_spb)

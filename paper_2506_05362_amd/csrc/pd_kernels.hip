@@ -13,7 +13,9 @@
 //            lattice offset in the horizon stencil.  Bond memory lives in the
 //            word itself: a bond that breaks is rewritten to node_i with the
 //            zero-force class, which is also what padding entries hold, so the
-//            step kernel needs no separate broken-flag reads.
+//            step kernel needs no separate broken-flag reads.  The slice path's steps
+//            read a second set of rows, in which the lanes of a slice hold the
+//            same class at the same entry (k_align), and write breaks to both.
 //
 // Each lane owns one node and evaluates its row in order (gather formulation,
 // Sec. 3.1 eq. (peri-damage) with nodal quadrature, Sec. 6.1): no atomics, so
@@ -226,6 +228,90 @@ __global__ __launch_bounds__(kBlock) void k_bond_fill(BuildArgs b) {
     for (int k = 0; k < W; ++k) col[(int64_t)k * kWave] = b.sentinel_hi;
   }
   for (int k = 0; k < W; ++k) orig[(int64_t)k * kWave] = col[(int64_t)k * kWave];
+}
+
+// Lined rows: the lanes of a slice hold the same class of the same stencil table at
+// the same entry, and a lane that has no such bond a word with kBroken.  Each row keeps
+// its order, so a node's sum is the same.  In the compact rows the lanes of nodes near a
+// grain's surface run ahead of the others; lined up, the bond constants of an entry are
+// the same for the wavefront and come through scalar loads, and the neighbours of nodes
+// consecutive on a lattice line are consecutive.
+// One wavefront per slice merges its rows: the entry at hand is the first (table, axis
+// order, class) that any lane has next, classes ranked as rows of that order list them.
+// Where that takes more than half as many entries again as the widest row has, the
+// slice has no lined rows and keeps to the compact ones: grains of different tables or
+// axis orders meet in it (twice the entries; the longest wavefront then decides a
+// launch), or its nodes are in no lattice order.
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void k_align(AlignArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int64_t s = (int64_t)blockIdx.x * kSlicesPerBlock + (threadIdx.x >> 6);
+  if (s >= a.nslices) return;  // whole wavefront leaves together
+  const int64_t i = s * kWave + lane;
+  const bool valid = i < a.n;
+  const int len = valid ? a.rowlen[i] : 0;
+  const int64_t so = a.slice_off[s];
+  const int wide = (int)((a.slice_off[s + 1] - so) / kWave);
+  const int limit = wide + wide / 2;
+  const uint32_t* orig = a.colOrig + so + lane;
+  const uint32_t* live = a.colE + so + lane;
+  const int g = valid ? packed_grain(a.u[i].w) : 0;
+  const uint32_t table = (uint32_t)a.grains[g].cls * (uint32_t)(a.n_stencil + 1);
+  const int order = a.axis_order[g];
+  const int32_t* rank = a.axis_rank + order * a.n_stencil;
+  const uint32_t first = (uint32_t)(a.grains[g].cls * 6 + order) * (uint32_t)a.n_stencil;
+  const uint32_t none = (uint32_t)(s * kWave) | kBroken;
+  const uint32_t node_mask = (1u << a.node_bits) - 1u;
+  uint32_t* out = nullptr;
+  int32_t* row = nullptr;
+  int W = 0;
+  if (FILL) {
+    const int64_t o = a.off[s];
+    W = (int)((a.off[s + 1] - o) / kWave);
+    if (W == 0) return;
+    out = a.lined + o + lane;
+    row = a.row + o / kWave;
+  }
+  int k = 0, p = 0;
+  uint32_t w = 0u, wn = 0u, l = 0u, ln = 0u;  // entries k and k + 1 as built and as they are now
+  auto entry = [&](int q, uint32_t& o, uint32_t& e) {
+    if (q >= len) return;
+    o = orig[(int64_t)q * kWave];
+    if (FILL) e = live[(int64_t)q * kWave];
+  };
+  entry(0, w, l);
+  entry(1, wn, ln);
+  for (;; ++p) {
+    const uint32_t key = k < len ? first + (uint32_t)rank[w >> a.node_bits] : 0xffffffffu;
+    uint32_t m = key;
+    for (int o = 32; o > 0; o >>= 1) m = min(m, (uint32_t)__shfl_xor((int)m, o, kWave));
+    if (m == 0xffffffffu || p >= (FILL ? W : limit + 1)) break;
+    const bool take = key == m;
+    if (FILL) {
+      // a lane without this bond names the neighbour of the nearest lane that has it (a
+      // lower one if there is), whose cache line is fetched anyway
+      const uint64_t has = __ballot(take);
+      const uint64_t below = has & ((1ull << lane) - 1ull);
+      const int src = take ? lane : below ? 63 - __clzll((long long)below) : __ffsll((unsigned long long)has) - 1;
+      const uint32_t j = (uint32_t)__shfl((int)(w & node_mask), src, kWave);
+      out[(int64_t)p * kWave] = take && l == w ? j : j | kBroken;
+      if (take) row[p] = (int32_t)((table + (w >> a.node_bits)) * (uint32_t)sizeof(StencilC));  // (all the same)
+    }
+    if (take) {
+      ++k;
+      w = wn;
+      l = ln;
+      entry(k + 1, wn, ln);
+    }
+  }
+  if (FILL) {
+    for (; p < W; ++p) {
+      out[(int64_t)p * kWave] = none;
+      if (lane == 0) row[p] = 0;
+    }
+  } else if (lane == 0) {
+    a.off[s] = p > limit ? 0 : (int64_t)((p + kBatch - 1) / kBatch * kBatch) * kWave;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -512,14 +598,9 @@ __device__ __forceinline__ NodeVA load_va(const StepArgs& A, int64_t i, bool val
   return r;
 }
 
-// Is the bond from node i to node j (same grain) intact after this evaluation's
-// breaks?  The node's built entries are sorted by neighbour index, so a binary
-// search finds j's entry; a pair with no entry (outside the horizon, or cut)
-// has no bond.  The bond memory is the live column word on the slice path
-// (perm < 0) and, on the tiled path, the node's lane bit in the lane mask of
-// its class in the grain's axis order perm (the tile kernel stores a class's
-// mask as soon as a bond of it breaks, before any node's tail).
-__device__ __forceinline__ bool bond_intact(const StepArgs& A, int64_t i, int j, int perm) {
+// The entry of the bond from node i to node j in the compact rows, -1 if there is
+// none: the node's entries as built are sorted by neighbour index.
+__device__ __forceinline__ int64_t bond_entry(const StepArgs& A, int64_t i, int j) {
   const uint32_t node_mask = (1u << A.node_bits) - 1u;
   const int64_t base = A.slice_off[i >> 6] + (i & 63);
   int lo = 0, hi = A.rowlen[i] - 1;
@@ -533,13 +614,26 @@ __device__ __forceinline__ bool bond_intact(const StepArgs& A, int64_t i, int j,
     } else if (jm > j) {
       hi = mid - 1;
     } else {
-      if (perm < 0) return A.colE[at] == wo;
-      const int b = A.ctob[perm * A.n_stencil + (int)(wo >> A.node_bits)];
-      const int32_t sl = A.slot[i];
-      return ((A.lmask[(int64_t)(sl >> 6) * kTileClasses + b] >> (sl & 63)) & 1ull) != 0ull;
+      return at;
     }
   }
-  return false;
+  return -1;
+}
+
+// Is the bond from node i to node j (same grain) intact after this evaluation's
+// breaks?  A pair with no entry (outside the horizon, or cut) has no bond.  The
+// bond memory is the live column word on the slice path
+// (perm < 0) and, on the tiled path, the node's lane bit in the lane mask of
+// its class in the grain's axis order perm (the tile kernel stores a class's
+// mask as soon as a bond of it breaks, before any node's tail).
+__device__ __forceinline__ bool bond_intact(const StepArgs& A, int64_t i, int j, int perm) {
+  const int64_t at = bond_entry(A, i, j);
+  if (at < 0) return false;
+  const uint32_t wo = A.colOrig[at];
+  if (perm < 0) return A.colE[at] == wo;
+  const int b = A.ctob[perm * A.n_stencil + (int)(wo >> A.node_bits)];
+  const int32_t sl = A.slot[i];
+  return ((A.lmask[(int64_t)(sl >> 6) * kTileClasses + b] >> (sl & 63)) & 1ull) != 0ull;
 }
 
 // Repulsion of node j on node i when closer than R_c (Sec. 3.2), with normal
@@ -624,11 +718,12 @@ __device__ __forceinline__ WallIn wall_in(const WallDev* walls, int w) {
 }
 
 // EXTRA = false compiles out self-contact and the wall-corner corrections (the
-// tiled kernel's variant for runs with neither); SCALAR_WALLS: see wall_in.
+// tiled kernel's variant for runs with neither); SCALAR_WALLS: see wall_in; SPLIT
+// also writes the split copy of u.
 // Bound by the latency of its dependent loads, so none of them sits behind a
 // branch that another one could have been issued before (the compiler waits for
 // every outstanding load where branches join).
-template <int MODE, bool EXTRA, bool SCALAR_WALLS>
+template <int MODE, bool EXTRA, bool SCALAR_WALLS, bool SPLIT>
 __device__ __forceinline__ void node_tail(const StepArgs& A, int64_t i, bool valid, const double4& ui,
                                           const GrainC* G, int ix, int iy, int iz, double fx, double fy,
                                           double fz, int nbroke, bool col_ok, int64_t col, const NodeVA& va,
@@ -808,6 +903,10 @@ __device__ __forceinline__ void node_tail(const StepArgs& A, int64_t i, bool val
         un.z = fma(hdt2, anz, fma(dt, vz, ui.z));
       }
       A.unext[i] = un;
+      if (SPLIT) {
+        A.uxy_next[i] = make_double2(un.x, un.y);
+        A.uz_next[i] = un.z;
+      }
       if (vdep) {
         // the next evaluation's damping and friction see v_{n+1} + dt/2 a_{n+1}
         A.vh_next[i] = fixed ? make_double4(0.0, 0.0, 0.0, 0.0)
@@ -826,27 +925,14 @@ __device__ __forceinline__ double far_coef(const StencilC& S, double d, double x
   return fabs(x) <= kPolyRange ? (S.civ * x) * q_long(x) : ce;
 }
 
-template <int MODE, bool ABS, int SPB, int DEPTH, bool SCALAR_WALLS>
-__device__ __forceinline__ void step_body(const StepArgs& A, const StencilC* s_st, int64_t blk) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
-  const int64_t slice = A.slice_base + blk * SPB + wid;
-  const bool slice_ok = slice < A.slice_end;
-  const int64_t i = slice * kWave + lane;
-  const bool valid = slice_ok && i >= A.node_lo && i < A.node_hi;
-
-  double4 ui = make_double4(0.0, 0.0, 0.0, 0.0);
-  if (valid) ui = A.ucur[i];
-  const int pi = packed_ijk(ui.w);
-  const int gi = valid ? packed_grain(ui.w) : 0;
-  const GrainC* G = A.grains + gi;
+// The bond sum of a slice over the compact rows, their tables in LDS.
+template <int MODE, bool ABS, int DEPTH>
+__device__ __forceinline__ void bonds_compact(const StepArgs& A, const StencilC* s_st, int64_t slice, bool slice_ok,
+                                              int64_t i, int lane, bool valid, const double4& ui, const GrainC* G,
+                                              double& fx, double& fy, double& fz, int& nbroke) {
   const double thr_x = G->thr_x, lo_x = G->lo_x;
-  const int ix = unpack_x(pi), iy = unpack_y(pi), iz = unpack_z(pi);
   const uint32_t node_mask = (1u << A.node_bits) - 1u;
   const int node_bits = A.node_bits;
-
-  double fx = 0.0, fy = 0.0, fz = 0.0;
-  int nbroke = 0;
 
   // ---- peridynamic bonds with bond memory ----
   // A row is taken kBatch entries at a time (slice widths are multiples of it), as
@@ -950,9 +1036,185 @@ __device__ __forceinline__ void step_body(const StepArgs& A, const StencilC* s_s
       }
     }
   }
+}
 
-  node_tail<MODE, true, SCALAR_WALLS>(A, i, valid, ui, G, ix, iy, iz, fx, fy, fz, nbroke, slice_ok,
-                  A.partial_base + (slice - A.slice_base), load_va(A, i, valid), -1);
+// f += coef y on the lanes of the scalar mask m, which needs no selection of coef:
+// lanes whose bond is gone (or breaks) are switched off for the three additions
+__device__ __forceinline__ void add_on_lanes(uint64_t m, double coef, double yx, double yy, double yz, double& fx,
+                                             double& fy, double& fz) {
+  uint64_t saved;
+  asm volatile(
+      "s_and_saveexec_b64 %3, %4\n\t"
+      "v_fma_f64 %0, %5, %6, %0\n\t"
+      "v_fma_f64 %1, %5, %7, %1\n\t"
+      "v_fma_f64 %2, %5, %8, %2\n\t"
+      "s_mov_b64 exec, %3"
+      : "+v"(fx), "+v"(fy), "+v"(fz), "=&s"(saved)
+      : "s"(m), "v"(coef), "v"(yx), "v"(yy), "v"(yz)
+      : "scc");
+}
+
+// Tables read through the constant address space: they are the same for the
+// whole wavefront (and change in no launch that reads them), so these become
+// scalar loads.
+typedef const __attribute__((address_space(4))) StencilC* TileTab;
+typedef int Rows4 __attribute__((ext_vector_type(4)));
+static_assert(kBatch == 4, "a batch's table rows come with one load");
+
+__device__ __forceinline__ bool lined_up(const StepArgs& A, int64_t slice) {
+  return A.lined_off[slice + 1] != A.lined_off[slice];
+}
+
+// The bond sum of a slice over its lined rows: the arithmetic and the order of
+// bonds_compact, with the entry's constants in scalar registers (an entry ahead) and
+// its live lanes in a lane mask.  Pipelined like it.  The vector cache bounds it, at one
+// 64-byte line a cycle: 60 lines an entry, 102 over compact rows (u as (x, y) and z, so
+// that a line holds four and eight nodes instead of two: 66 instead of 78; lanes
+// without the bond reading a neighbour's line: 60 instead of 66).  523,690 nodes in 125
+// spheres: 149 us a launch instead of 204.
+template <int MODE, bool ABS, int DEPTH>
+__device__ __forceinline__ void bonds_lined(const StepArgs& A, int64_t slice, int64_t i, int lane, bool valid,
+                                            const double4& ui, const GrainC* G, double& fx, double& fy,
+                                            double& fz, int& nbroke) {
+  const int64_t off = A.lined_off[slice];
+  const int W = (int)((A.lined_off[slice + 1] - off) >> 6);
+  const int nb = W / kBatch;
+  const double thr_x = G->thr_x, lo_x = G->lo_x;
+  uint32_t* cp = A.lined + off + lane;
+  const int32_t* rows = A.lined_row + (off >> 6);
+  const char* xybase = reinterpret_cast<const char*>(A.uxy);
+  const char* zbase = reinterpret_cast<const char*>(A.uz);
+  const char* tbase = reinterpret_cast<const char*>(A.stencil);
+  const uint64_t mine = __ballot(valid);
+  constexpr int CR = 2 * DEPTH;  // batches of column words held
+  uint32_t cw[CR][kBatch];
+  double ux[DEPTH][kBatch], uy[DEPTH][kBatch], uz[DEPTH][kBatch];
+  const PolyS P = poly_in_registers();
+  auto columns = [&](int b, uint32_t (&c)[kBatch]) {
+    const uint32_t* q = cp + (b < nb ? b : nb - 1) * (kBatch * kWave);
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) c[u] = q[u * kWave];
+  };
+  auto gather = [&](const uint32_t (&c)[kBatch], int r) {
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const double2 q = *reinterpret_cast<const double2*>(xybase + (c[u] << 4));  // (drops the flags)
+      ux[r][u] = q.x;
+      uy[r][u] = q.y;
+      uz[r][u] = *reinterpret_cast<const double*>(zbase + (c[u] << 3));
+    }
+  };
+  struct RowK {
+    double hx, hy, hz, inv, civ;
+  };
+  // the places of the first 128 entries' table rows, across the lanes (every wait for a
+  // scalar load is a wait for all of them, and these would miss the caches)
+  const int32_t r0 = rows[lane < W ? lane : W - 1], r1 = rows[lane + kWave < W ? lane + kWave : W - 1];
+  auto list = [&](int b) {
+    if (b < 2 * kWave / kBatch) {
+      const int32_t r = b < kWave / kBatch ? r0 : r1;
+      const int l = b % (kWave / kBatch) * kBatch;
+      return Rows4{__builtin_amdgcn_readlane(r, l), __builtin_amdgcn_readlane(r, l + 1),
+                   __builtin_amdgcn_readlane(r, l + 2), __builtin_amdgcn_readlane(r, l + 3)};
+    }
+    const int32_t* p = rows + (b < nb ? b : nb - 1) * kBatch;
+    asm volatile("" : "+s"(p));  // (keeps the load here)
+    return *(const __attribute__((address_space(4))) Rows4*)p;
+  };
+  auto row_at = [&](int at) {
+    const char* p = tbase + at;
+    asm volatile("" : "+s"(p));  // (keeps the loads here)
+    const TileTab t = (TileTab)p;
+    return RowK{t->hx, t->hy, t->hz, t->inv_l0sq, t->civ};
+  };
+  Rows4 rc, rn = list(0);
+  RowK S = row_at(rn[0]);
+  auto batch = [&](int b, const uint32_t (&c)[kBatch], int r) {
+    rc = rn;
+    rn = list(b + 1);
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const double ex = ux[r][u] - ui.x, ey = uy[r][u] - ui.y, ez = uz[r][u] - ui.z;
+      const double yx = S.hx + ex, yy = S.hy + ey, yz = S.hz + ez;  // y = xi + eta
+      // |y|^2 - |xi|^2 = eta . (2 xi + eta)
+      const double d = fma(ex, fma(2.0, S.hx, ex), fma(ey, fma(2.0, S.hy, ey), ez * fma(2.0, S.hz, ez)));
+      const double x = d * S.inv;
+      bool over = x > thr_x;
+      if (ABS) over = over || x < lo_x;
+      const double civ = S.civ, cx = civ * x;
+      S = row_at(u + 1 < kBatch ? rc[(u + 1) % kBatch] : rn[0]);
+      double coef = cx * q_short(x, P);
+      const uint64_t live = __ballot((int32_t)c[u] >= 0);
+      const bool far = !(fabs(x) <= kShortRange);
+      if (__builtin_expect((__ballot(far) & live) != 0ull, 0)) {
+        const bool exact = !(fabs(x) <= kPolyRange);
+        double cl = cx * q_long(x);
+        if (__builtin_expect((__ballot(exact) & live) != 0ull, 0)) {
+          const TileTab t = (TileTab)(tbase + rc[u]);
+          const double lsq = t->l0sq + d;
+          const double l = lsq * rsqrt_full(lsq);
+          const double ce = civ * (d * rcp_full(fma(l, t->l0, lsq)));
+          cl = exact ? ce : cl;
+        }
+        coef = far ? cl : coef;
+      }
+      const uint64_t ov = __ballot(over);
+      add_on_lanes(live & ~ov, coef, yx, yy, yz, fx, fy, fz);
+      if (__builtin_expect(MODE != MODE_FORCE_ONLY && (live & ov & mine) != 0ull, 0)) {
+        if (over && valid && (int32_t)c[u] >= 0) {
+          cp[(b * kBatch + u) * kWave] = c[u] | kBroken | kFresh;  // the bond stays broken from now on
+          ++nbroke;
+        }
+      }
+    }
+  };
+#pragma unroll
+  for (int b = 0; b < CR - 1; ++b) columns(b, cw[b]);
+#pragma unroll
+  for (int b = 0; b < DEPTH - 1; ++b) gather(cw[b], b);
+  for (int b0 = 0; b0 < nb; b0 += CR) {
+#pragma unroll
+    for (int r = 0; r < CR; ++r) {
+      if (b0 + r >= nb) break;
+      columns(b0 + r + CR - 1, cw[(r + CR - 1) % CR]);
+      gather(cw[(r + DEPTH - 1) % CR], (r + DEPTH - 1) % DEPTH);
+      batch(b0 + r, cw[r], r % DEPTH);
+    }
+  }
+  // the compact rows follow
+  if (MODE != MODE_FORCE_ONLY && __ballot(nbroke > 0) != 0ull) {
+    if (nbroke > 0) {
+      for (int p = 0; p < W; ++p) {
+        const uint32_t w = cp[(int64_t)p * kWave];
+        if (!(w & kFresh)) continue;
+        A.colE[bond_entry(A, i, (int)(w & ~(kBroken | kFresh)))] = (uint32_t)i | A.sentinel_hi;
+        cp[(int64_t)p * kWave] = w & ~kFresh;
+      }
+    }
+  }
+}
+
+template <int MODE, bool ABS, int SPB, int DEPTH, bool SCALAR_WALLS, bool LINED>
+__device__ __forceinline__ void step_body(const StepArgs& A, const StencilC* s_st, int64_t blk) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
+  const int64_t slice = A.slice_base + blk * SPB + wid;
+  const bool slice_ok = slice < A.slice_end;
+  const int64_t i = slice * kWave + lane;
+  const bool valid = slice_ok && i >= A.node_lo && i < A.node_hi;
+
+  double4 ui = make_double4(0.0, 0.0, 0.0, 0.0);
+  if (valid) ui = A.ucur[i];
+  const int pi = packed_ijk(ui.w);
+  const GrainC* G = A.grains + (valid ? packed_grain(ui.w) : 0);
+  double fx = 0.0, fy = 0.0, fz = 0.0;
+  int nbroke = 0;
+  if (LINED && slice_ok && lined_up(A, slice))
+    bonds_lined<MODE, ABS, DEPTH>(A, slice, i, lane, valid, ui, G, fx, fy, fz, nbroke);
+  else
+    bonds_compact<MODE, ABS, DEPTH>(A, s_st, slice, slice_ok, i, lane, valid, ui, G, fx, fy, fz, nbroke);
+  node_tail<MODE, true, SCALAR_WALLS, LINED>(A, i, valid, ui, G, unpack_x(pi), unpack_y(pi), unpack_z(pi), fx, fy, fz, nbroke,
+                                      slice_ok, A.partial_base + (slice - A.slice_base), load_va(A, i, valid), -1);
 }
 
 __device__ __forceinline__ void stage_stencil(const StepArgs& A, StencilC* s_st) {
@@ -964,14 +1226,21 @@ __device__ __forceinline__ void stage_stencil(const StepArgs& A, StencilC* s_st)
 // DEPTH 2 in 128 registers, so that four wavefronts a SIMD stay resident; DEPTH 4
 // for meshes that leave a SIMD two wavefronts or fewer, whose only cover for a
 // gather is their own other gathers.
-template <int MODE, bool ABS, int SPB, int DEPTH>
+template <int MODE, bool ABS, int SPB, int DEPTH, bool LINED>
 __global__ __launch_bounds__(SPB * kWave) __attribute__((amdgpu_waves_per_eu(DEPTH > 2 ? 2 : PD_STEP_WAVES_PER_EU)))
 void k_step(StepArgs A) {
   extern __shared__ StencilC s_st[];
   if (MODE == MODE_STEP && halted(A.halt)) return;
-  stage_stencil(A, s_st);
   const int64_t blk = A.xcd_remap ? xcd_remap(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-  step_body<MODE, ABS, SPB, DEPTH, true>(A, s_st, blk);
+  bool tables = !LINED;
+  if (LINED)
+#pragma unroll
+    for (int w = 0; w < SPB; ++w) {
+      const int64_t s = A.slice_base + blk * SPB + w;
+      tables = tables || (s < A.slice_end && !lined_up(A, s));
+    }
+  if (tables) stage_stencil(A, s_st);  // (the same for the workgroup)
+  step_body<MODE, ABS, SPB, DEPTH, true, LINED>(A, s_st, blk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1024,10 +1293,6 @@ constexpr int tile_comp(int k, int perm, int axis) {
   return kAxisOrder[perm][0] == axis ? c.d[0] : kAxisOrder[perm][1] == axis ? c.d[1] : c.d[2];
 }
 
-// Tables read through the constant address space: they are the same for the
-// whole wavefront (and change in no launch that reads them), so these become
-// scalar loads.
-typedef const __attribute__((address_space(4))) StencilC* TileTab;
 typedef const __attribute__((address_space(4))) TileNorms* NormTab;
 typedef const __attribute__((address_space(4))) uint64_t* MaskTab;
 
@@ -1092,22 +1357,6 @@ __device__ __forceinline__ void tile_load(const double* L, const double* Lz, con
     in.hy = row->hy;
     in.hz = row->hz;
   }
-}
-
-// f += coef y on the lanes of the scalar mask m, which needs no selection of coef:
-// lanes whose bond is gone (or breaks) are switched off for the three additions
-__device__ __forceinline__ void add_on_lanes(uint64_t m, double coef, double yx, double yy, double yz, double& fx,
-                                             double& fy, double& fz) {
-  uint64_t saved;
-  asm volatile(
-      "s_and_saveexec_b64 %3, %4\n\t"
-      "v_fma_f64 %0, %5, %6, %0\n\t"
-      "v_fma_f64 %1, %5, %7, %1\n\t"
-      "v_fma_f64 %2, %5, %8, %2\n\t"
-      "s_mov_b64 exec, %3"
-      : "+v"(fx), "+v"(fy), "+v"(fz), "=&s"(saved)
-      : "s"(m), "v"(coef), "v"(yx), "v"(yy), "v"(yz)
-      : "scc");
 }
 
 // e + SCALE xi for a component of xi that is C spacings: nothing to add at zero
@@ -1305,7 +1554,7 @@ __global__ __launch_bounds__(kTS * kWave) __attribute__((amdgpu_waves_per_eu(4))
   }
   // the prefetch's data is not needed; consuming it keeps the load
   asm volatile("" ::"v"(mpre.x ^ mpre.y ^ mpre.z ^ mpre.w));
-  node_tail<MODE_STEP, EXTRA, true>(A, i, valid, ui, G, unpack_x(pi), unpack_y(pi), unpack_z(pi), fx, fy, fz, nbroke,
+  node_tail<MODE_STEP, EXTRA, true, false>(A, i, valid, ui, G, unpack_x(pi), unpack_y(pi), unpack_z(pi), fx, fy, fz, nbroke,
                               true, (int64_t)kTS * t + wid, load_va(A, i, valid), TG.perm);
 }
 
@@ -1624,7 +1873,7 @@ void k_step_persistent(StepArgs A, int64_t nsteps, BarrierArgs B) {
     for (int64_t q = 0; q < rounds; ++q) {
       const int64_t p = p0 + q * pstep;
       const int64_t vb1 = nv * (p + 1) / np;
-      for (int64_t vb = nv * p / np; vb < vb1; ++vb) step_body<MODE_STEP, ABS, 4, 2, false>(A, s_st, vb);
+      for (int64_t vb = nv * p / np; vb < vb1; ++vb) step_body<MODE_STEP, ABS, 4, 2, false, false>(A, s_st, vb);
     }
     if (grid_arrive(B, gridDim.x, A.status, &s_last)) {
       // level (1) by this workgroup's wavefronts, then level (2)
@@ -2372,6 +2621,14 @@ __global__ void k_unpack_u(const double4* u4, double* out, int64_t n) {
   out[2 * n + i] = u.z;
 }
 
+__global__ void k_split_u(const double4* u4, double2* uxy, double* uz, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double4 u = u4[i];
+  uxy[i] = make_double2(u.x, u.y);
+  uz[i] = u.z;
+}
+
 __global__ void k_damage(const int32_t* intact, const int32_t* initial, double* out, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -2382,6 +2639,12 @@ __global__ void k_damage(const int32_t* intact, const int32_t* initial, double* 
 hipError_t launch_unpack_u(const double4* u4, double* out, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_unpack_u, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, u4, out, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_u(const double4* u4, double2* uxy, double* uz, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_split_u, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, u4, uxy, uz, n);
   return hipGetLastError();
 }
 
@@ -2461,6 +2724,17 @@ hipError_t launch_bond_fill(const BuildArgs& b, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_align_width(const AlignArgs& a, hipStream_t s) {
+  if (a.nslices == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_align<false>, dim3(grid_for(a.nslices, kSlicesPerBlock)), dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t launch_align_fill(const AlignArgs& a, hipStream_t s) {
+  if (a.nslices == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_align<true>, dim3(grid_for(a.nslices, kSlicesPerBlock)), dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
 int32_t step_blocks_spb(int64_t nslices, int slices_per_block) {
   return (int32_t)grid_for(nslices, slices_per_block);
 }
@@ -2481,11 +2755,11 @@ static size_t step_lds(const StepArgs& a) {
   return sizeof(StencilC) * (size_t)(a.n_stencil + 1) * (size_t)a.n_classes;
 }
 
-template <int MODE, int SPB, int DEPTH>
+template <int MODE, int SPB, int DEPTH, bool LINED>
 static void launch_step_d(const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const int32_t nb = step_blocks_spb(a.slice_end - a.slice_base, SPB);
   if (nb == 0) return;
-  void (*kern)(StepArgs) = a.abs_stretch ? k_step<MODE, true, SPB, DEPTH> : k_step<MODE, false, SPB, DEPTH>;
+  void (*kern)(StepArgs) = a.abs_stretch ? k_step<MODE, true, SPB, DEPTH, LINED> : k_step<MODE, false, SPB, DEPTH, LINED>;
   // with events, the launch itself records them around the kernel
   if (e0 || e1) hipExtLaunchKernelGGL(kern, dim3(nb), dim3(SPB * kWave), step_lds(a), s, e0, e1, 0, a);
   else hipLaunchKernelGGL(kern, dim3(nb), dim3(SPB * kWave), step_lds(a), s, a);
@@ -2496,8 +2770,12 @@ static void launch_step_d(const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEv
 constexpr int64_t kDeepSlices = 1024;
 template <int MODE, int SPB>
 static void launch_step_t(const StepArgs& a, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
-  if (MODE == MODE_STEP && a.slice_end - a.slice_base <= kDeepSlices) launch_step_d<MODE, SPB, 4>(a, s, e0, e1);
-  else launch_step_d<MODE, SPB, 2>(a, s, e0, e1);
+  const bool deep = a.slice_end - a.slice_base <= kDeepSlices;
+  if constexpr (MODE == MODE_STEP) {
+    if (a.lined) return launch_step_d<MODE, SPB, 2, true>(a, s, e0, e1);
+    if (deep) return launch_step_d<MODE, SPB, 4, false>(a, s, e0, e1);
+  }
+  launch_step_d<MODE, SPB, 2, false>(a, s, e0, e1);
 }
 
 hipError_t launch_step(const StepArgs& a, int mode, hipStream_t s) {
