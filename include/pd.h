@@ -300,7 +300,8 @@ pd_status pd_loop_counts(pd_ctx* ctx, int64_t* out6);
                          reduces the wall reactions;
      PD_LOOP_PER_GRAIN   unbatched reference: one launch per grain per step.
    slices_per_block: 64-node slices (wavefronts) per workgroup, 1, 2, 4 or 8
-   (GRAPH and DIRECT; the others use 4).  xcd_remap: 1 maps consecutive
+   (GRAPH and DIRECT; the others use 4); fewer where that would leave compute
+   units without a workgroup.  xcd_remap: 1 maps consecutive
    workgroups to contiguous slice ranges per XCD, 0 keeps dispatch order.
    persistent_blocks: workgroups of the persistent launch, 0 = as many as can be
    resident.
