@@ -102,6 +102,7 @@ struct pd_ctx {
   uint32_t* colOrig = nullptr;
   // the step's own rows on the slice path (null: it reads colE, which follows their bond memory)
   uint32_t* lined = nullptr;
+  bool lined_asked = false;  // made, or found not to be had, since the path was chosen
   int64_t* lined_off = nullptr;
   int32_t* lined_row = nullptr;
   std::vector<int> axis_order;  // per grain, -1 in no lattice order
@@ -663,7 +664,7 @@ int lattice_order(const pd_ctx* c, int32_t g) {
   return -1;
 }
 
-// axis_order, and on the device the place of every horizon class in rows of each order
+// For lined rows: axis_order, and on the device the place of every horizon class in rows of each order
 // (stencil: the offsets, packed and lexicographic)
 pd_status rank_classes(pd_ctx* c, const std::vector<int32_t>& stencil) {
   c->axis_order.resize((size_t)c->n_grains);
@@ -713,7 +714,7 @@ pd_status build_tiles(pd_ctx* c) {
   std::vector<std::array<int, 3>> glo((size_t)G), ghi((size_t)G);
   for (int32_t g = 0; g < G; ++g) {
     const int64_t b = c->grain_begin[(size_t)g], e = c->grain_begin[(size_t)g + 1];
-    const int perm = c->axis_order[(size_t)g];
+    const int perm = c->axis_order.empty() ? lattice_order(c, g) : c->axis_order[(size_t)g];
     if (perm < 0) return PD_OK;  // this grain's node order is not a lattice order
     int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {0, 0, 0};
     for (int64_t i = b; i < e; ++i)
@@ -988,8 +989,11 @@ bool lines_rows(const pd_launch& l) { return l.bond_path == PD_BONDS_SLICES && l
 // The lined rows and the split copy of u, for meshes that gain by them.  Without the
 // memory for them (about as much as colE takes), or with no slice that lines up, the
 // steps read colE alone.
+// Made by the first pd_step that reads them: contexts that change to the tile path
+// after the build never need them.
 pd_status make_lined(pd_ctx* c) {
-  drop_lined(c);
+  if (c->lined_asked || !lines_rows(c->launch)) return PD_OK;
+  c->lined_asked = true;
   if (c->nslices < kLinedSlices || c->n > kLinedNodes) return PD_OK;
   hipStream_t s = c->stream;
   auto get = [&](auto** p, int64_t n) {
@@ -1532,7 +1536,7 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
     c->pg_part_base[(size_t)g] = c->pg_cols;
     c->pg_cols += c->pg_slice_hi[(size_t)g] - c->pg_slice_lo[(size_t)g];
   }
-  TRY(rank_classes(c, stencil));
+  if (c->nslices >= kLinedSlices) TRY(rank_classes(c, stencil));
   TRY(build_tiles(c));
   c->partial_cols = std::max<int64_t>(std::max<int64_t>(std::max<int64_t>(c->nslices, c->pg_cols), kTS * c->n_tiles), 1);
   TRY(alloc_n(c, &c->wall_partial, c->partial_cols * 3 * std::max(c->n_walls, 1), "wall partials"));
@@ -1548,7 +1552,6 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
   HIPCHK(c, launch_wall_corners(A, 0, s));
   HIPCHK(c, launch_step(A, MODE_FIRST, s));
   HIPCHK(c, launch_wall_finalize(A, s));
-  if (lines_rows(c->launch)) TRY(make_lined(c));
   c->built = 1;
   c->step = 0;
   return report_status(c);
@@ -1559,6 +1562,7 @@ pd_status pd_step(pd_ctx* c, int64_t n_steps) {
   Range r("pd_step");
   if (!c->built) return fail(c, PD_ERR_STATE, "pd_build_bonds must come first");
   if (n_steps < 0) return fail(c, PD_ERR_INVALID, "n_steps < 0");
+  if (n_steps > 0) TRY(make_lined(c));
   int64_t left = n_steps;
   const int64_t step0 = c->step;
   const bool watch = early_rebuilds(c);
@@ -1638,9 +1642,9 @@ pd_status pd_set_launch(pd_ctx* c, const pd_launch* l) {
     else TRY(sync_columns(c));
     HIPCHK(c, hipStreamSynchronize(c->stream));
   }
-  if (c->built && lines_rows(*l) != lines_rows(c->launch)) {
-    if (lines_rows(*l)) TRY(make_lined(c));
-    else drop_lined(c);
+  if (!lines_rows(*l)) {
+    drop_lined(c);
+    c->lined_asked = false;
   }
   c->launch = *l;
   return PD_OK;

@@ -37,6 +37,7 @@ def test_lined_rows_bitwise_equal_to_compact(name):
     a.step(20)
     b.step(20)
     blob = a.get_state()
+    c.step(3)
     c.set_state(blob)                       # onto lined rows, with broken bonds
     a.set_launch(bond_path=pd.BONDS_TILES)  # lined -> masks
     a.step(5)
