@@ -2089,16 +2089,21 @@ __global__ __launch_bounds__(256) void k_skin_box(ContactArgs c, int check) {
 }
 
 // is any other grain's box within the cutoff?  One wavefront per grain, the
-// others tested 64 at a time; with self-contact no grain is isolated.
+// others tested 64 at a time; with self-contact no grain is isolated, but for one
+// without nodes or with a position that is not a number on any axis: such a box
+// does not bound its nodes, which must then not be binned (the step flags them).
 __global__ __launch_bounds__(kWave) void k_isolated(ContactArgs c, double cut) {
   const int a = blockIdx.x, lane = threadIdx.x;
   double alo[3], ahi[3];
+  bool box = true;
   for (int q = 0; q < 3; ++q) {
-    alo[q] = ord_val(c.gbox[6 * a + q]) - cut;
-    ahi[q] = ord_val(c.gbox[6 * a + 3 + q]) + cut;
+    const double lo = ord_val(c.gbox[6 * a + q]), hi = ord_val(c.gbox[6 * a + 3 + q]);
+    box = box && lo <= hi;
+    alo[q] = lo - cut;
+    ahi[q] = hi + cut;
   }
-  bool near = c.self_contact && alo[0] <= ahi[0];
-  for (int b0 = 0; b0 < c.n_grains && !near; b0 += kWave) {
+  bool near = c.self_contact && box;
+  for (int b0 = 0; b0 < c.n_grains && box && !near; b0 += kWave) {
     const int b = b0 + lane;
     bool ov = b < c.n_grains && b != a;
     if (ov)
