@@ -1175,7 +1175,7 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
     gc.cVih = cc * gc.V / h;
     gc.conic_inv_delta = (P.flags & PD_FLAG_CONIC) ? 1.0 / delta : 0.0;
     gc.thr_x = s0 * (2.0 + s0);
-    gc.lo_x = -s0 * (2.0 - s0);
+    gc.lo_x = s0 < 1.0 ? -s0 * (2.0 - s0) : -INFINITY;  // no bond is compressed past its whole length
     gc.h = h;
     gc.rho = mt.density;
     gc.inv_rho = 1.0 / mt.density;

@@ -32,7 +32,7 @@ struct GrainC {
   double cVih;    // c * V / h (micromodulus, or c0 of the conic form, times nodal volume, over h)
   double conic_inv_delta;  // 1/delta with the conic micromodulus c0 (1 - |xi|/delta), else 0
   // a bond breaks when x = (|y|^2 - |xi|^2) / |xi|^2 > thr_x = (1 + s0)^2 - 1  (s > s0), with the
-  // |s| reading also when x < lo_x = (1 - s0)^2 - 1  (s < -s0)
+  // |s| reading also when x < lo_x = (1 - s0)^2 - 1  (s < -s0; never with s0 >= 1)
   double thr_x, lo_x;
   double h;
   double V;       // h^3
