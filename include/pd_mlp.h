@@ -56,7 +56,9 @@ pd_status pdm_set_adam(pdm_net* net, float beta1, float beta2, float eps, float 
    16 x 16 x 32 BF16 matrix-core instruction.  For dims {din <= 16, 256, 256, 256,
    dout <= 16} a fused path runs by default: one kernel with the hidden layers'
    weights in registers and the activations between them in LDS; its operands are
-   rounded to BF16 where the layer-by-layer path rounds them. */
+   rounded to BF16 where the layer-by-layer path rounds them.  y may overlap x for
+   batches up to max_batch; unless it is x itself with rows of the same length, such a
+   call takes the layer-by-layer kernels. */
 pd_status pdm_forward(pdm_net* net, const float* x, int64_t batch, float* y);
 /* Choose the inference path: fused != 0 selects the fused kernel (error
    PD_ERR_UNSUPPORTED when the dims or the device do not allow them), 0 the

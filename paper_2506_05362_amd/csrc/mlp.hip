@@ -867,7 +867,12 @@ pd_status pdm_set_inference(pdm_net* n, int32_t fused) {
 pd_status pdm_forward(pdm_net* n, const float* x, int64_t batch, float* y) {
   if (!n || (!x && batch > 0) || (!y && batch > 0) || batch < 0) return PD_ERR_INVALID;
   const int64_t din = n->dims.front(), dout = n->dims.back();
-  if (n->use_fused && batch > 0) {
+  // Workgroups of the fused kernel write outputs while others have yet to read their
+  // inputs.  Where the two arrays overlap the layer-by-layer kernels give the same
+  // values: they read a chunk's inputs before its outputs are written.  (Equal rows in
+  // place are one workgroup's own.)
+  const bool overlap = x < y + batch * dout && y < x + batch * din && !(x == y && din == dout);
+  if (n->use_fused && batch > 0 && !overlap) {
     Infer a{};
     a.x = x;
     a.M = batch;
