@@ -1762,16 +1762,14 @@ pd_status pd_get(pd_ctx* c, pd_field f, void* dst, int64_t dst_bytes, int32_t ds
     HIPCHK(c, hipStreamSynchronize(s));
     return PD_OK;
   };
-  // a field that a kernel makes: into dst itself, or by way of the field buffer
+  // a field that a kernel makes: into dst itself, or by way of the candidate scratch
+  // rows, which only a rebuild uses (40 bytes a node at least; these fields take 24)
   auto made = [&](auto launch) -> pd_status {
-    if (dst_on_device) {
-      HIPCHK(c, launch(static_cast<double*>(dst)));
-      HIPCHK(c, hipStreamSynchronize(s));
-      return PD_OK;
-    }
-    if (!c->F) TRY(alloc_n(c, &c->F, 3 * N, "field output"));
-    HIPCHK(c, launch(c->F));
-    return from_dev(c->F);
+    double* to = static_cast<double*>(dst_on_device ? dst : (void*)c->cand_scratch);
+    HIPCHK(c, launch(to));
+    if (!dst_on_device) return from_dev(to);
+    HIPCHK(c, hipStreamSynchronize(s));
+    return PD_OK;
   };
   switch (f) {
     case PD_DISPLACEMENT:
@@ -1779,7 +1777,7 @@ pd_status pd_get(pd_ctx* c, pd_field f, void* dst, int64_t dst_bytes, int32_t ds
     case PD_VELOCITY: return from_dev(c->v);
     case PD_ACCEL: return from_dev(c->a);
     case PD_FORCE_DENSITY: {
-      if (!c->F) TRY(alloc_n(c, &c->F, 3 * N, "field output"));
+      if (!c->F) TRY(alloc_n(c, &c->F, 3 * N, "force output"));
       TRY(sync_columns(c));  // the force-only pass reads the bond memory from the column words
       StepArgs A = step_args(c);
       HIPCHK(c, launch_wall_corners(A, 1, s));

@@ -1,0 +1,65 @@
+"""What the simulator asks its allocator for: reading fields out takes no device memory."""
+import numpy as np
+import pytest
+
+from paper_2506_05362_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+class Recorder:
+    """PyTorch's caching allocator and a stream; holds the sizes in use, and can refuse."""
+
+    def __init__(self):
+        from paper_2506_05362_amd import pd
+        base = pd.TorchPlumbing()
+        self.torch, self.device, self.stream, self.stream_ptr = base.torch, base.device, base.stream, base.stream_ptr
+        self.sizes, self.refuse, self.refused = {}, False, 0
+
+        def _alloc(nbytes, user):
+            if self.refuse:
+                self.refused += 1
+                return None
+            p = self.torch.cuda.caching_allocator_alloc(int(nbytes), self.device, self.stream)
+            self.sizes[p] = int(nbytes)
+            return p
+
+        def _free(ptr, user):
+            del self.sizes[ptr]
+            self.torch.cuda.caching_allocator_delete(int(ptr))
+
+        self.alloc, self.free = pd.ALLOC_FN(_alloc), pd.FREE_FN(_free)
+
+    @property
+    def in_use(self):
+        return sum(self.sizes.values())
+
+
+def _mesh():
+    wl = I.two_spheres(radius_cells=6, speed=30.0, gap=0.0)
+    wl.v0[:] += np.random.default_rng(0).normal(0.0, 1.0, size=wl.v0.shape)
+    return wl
+
+
+def test_fields_without_device_memory():
+    """State, damage and counts come out, to host and device memory, when there is no device
+    memory left: the same values as where there is, and nothing is asked for."""
+    import torch
+    from paper_2506_05362_amd import pd
+    wl = _mesh()
+    mem = Recorder()
+    sim, other = pd.Sim(wl, plumbing=mem), pd.Sim(wl)
+    for s in (sim, other):
+        s.step(25)
+    mem.refuse = True
+    for name in ("displacement", "velocity", "accel", "damage", "intact_count", "initial_count"):
+        host = sim.get(name)
+        dev = torch.zeros(host.size, dtype=getattr(torch, str(host.dtype)), device="cuda")
+        sim.get_device(name, dev.data_ptr(), sim.field_bytes(name))
+        assert np.array_equal(host, other.get(name)), name
+        assert np.array_equal(dev.cpu().numpy(), host.ravel()), name
+    assert mem.refused == 0
+    for s in (sim, other):  # the read-outs left the candidates alone
+        s.step(25)
+    assert np.array_equal(sim.get("displacement"), other.get("displacement"))
+    sim.close()
