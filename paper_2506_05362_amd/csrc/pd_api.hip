@@ -126,6 +126,7 @@ struct pd_ctx {
   int64_t* scan64 = nullptr;
   double* energy_partial = nullptr;
   double* scratch_dev = nullptr;  // this context's GPU's copy of the allocation-free scratch
+  int device = 0;
   double* energy_out = nullptr;
   // measurement hook
   int timing = 0;
@@ -1083,6 +1084,7 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
       g_scratch_dev[dev] = static_cast<double*>(p);
     }
     c->scratch_dev = g_scratch_dev[dev];
+    c->device = dev;
   }
 
   const int64_t N = mesh->n_nodes;
@@ -1762,12 +1764,19 @@ pd_status pd_get(pd_ctx* c, pd_field f, void* dst, int64_t dst_bytes, int32_t ds
     HIPCHK(c, hipStreamSynchronize(s));
     return PD_OK;
   };
-  // a field that a kernel makes: into dst itself, or by way of the candidate scratch
-  // rows, which only a rebuild uses (40 bytes a node at least; these fields take 24)
+  // a field that a kernel makes: into dst itself where it is this GPU's memory and aligned
+  // (a copy needs neither), or by way of the candidate scratch rows, which only a rebuild
+  // uses (40 bytes a node at least; these fields take 24)
   auto made = [&](auto launch) -> pd_status {
-    double* to = static_cast<double*>(dst_on_device ? dst : (void*)c->cand_scratch);
+    bool direct = dst_on_device != 0 && (reinterpret_cast<uintptr_t>(dst) & 7u) == 0;
+    if (direct) {
+      hipPointerAttribute_t at{};
+      direct = hipPointerGetAttributes(&at, dst) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == c->device;
+      (void)hipGetLastError();
+    }
+    double* to = direct ? static_cast<double*>(dst) : reinterpret_cast<double*>(c->cand_scratch);
     HIPCHK(c, launch(to));
-    if (!dst_on_device) return from_dev(to);
+    if (!direct) return from_dev(to);
     HIPCHK(c, hipStreamSynchronize(s));
     return PD_OK;
   };

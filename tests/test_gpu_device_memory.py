@@ -1,4 +1,4 @@
-"""What the simulator asks its allocator for: reading fields out takes no device memory."""
+"""Device memory of the simulator: reading fields out takes none, and goes to any."""
 import numpy as np
 import pytest
 
@@ -62,4 +62,26 @@ def test_fields_without_device_memory():
     for s in (sim, other):  # the read-outs left the candidates alone
         s.step(25)
     assert np.array_equal(sim.get("displacement"), other.get("displacement"))
+    sim.close()
+
+
+def test_fields_into_any_device_memory():
+    """A destination at any byte of a device array, or in pinned host memory handed over as
+    device memory, is written as a copy would: the bytes around it stay."""
+    import torch
+    from paper_2506_05362_amd import pd
+    sim = pd.Sim(_mesh())
+    sim.step(20)
+    for name in ("displacement", "velocity", "damage"):
+        want = sim.get(name).tobytes()
+        for kind in ("device", "pinned"):
+            for off in (0, 1, 4, 8):
+                print(name, kind, off, flush=True)
+                buf = torch.full((len(want) + 16,), 7, dtype=torch.uint8,
+                                 **(dict(device="cuda") if kind == "device" else dict(pin_memory=True)))
+                sim.get_device(name, buf.data_ptr() + off, len(want))
+                torch.cuda.synchronize()
+                b = buf.cpu().numpy().tobytes()
+                assert b[:off] == b"\x07" * off and b[off + len(want):] == b"\x07" * (16 - off)
+                assert b[off:off + len(want)] == want, (name, kind, off)
     sim.close()
