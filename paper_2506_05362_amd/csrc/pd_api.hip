@@ -1478,10 +1478,8 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
   c->T = T;
   c->capacity = std::max<int64_t>((int64_t)c->cap_per_node * N, 1 << 16);
   c->scratch_w = 2 * c->cap_per_node;
-  TRY(alloc_n(c, &c->rec, 2 * N, "node records"));
   TRY(alloc_n(c, &c->spos, N, "binned positions"));
   TRY(alloc_n(c, &c->origin, 4, "cell grid origin"));
-  TRY(alloc_n(c, &c->rank, N, "ranks in buckets"));
   TRY(alloc_n(c, &c->srec, N, "binned records"));
   // the candidate scratch rows, written by the search; until the scatter has run
   // their memory holds what the binning hands it (40 bytes a node)

@@ -1,4 +1,5 @@
-"""Device memory of the simulator: reading fields out takes none, and goes to any."""
+"""Device memory of the simulator: none is asked for and left unused, reading fields out
+takes none, and goes to any."""
 import numpy as np
 import pytest
 
@@ -84,4 +85,41 @@ def test_fields_into_any_device_memory():
                 b = buf.cpu().numpy().tobytes()
                 assert b[:off] == b"\x07" * off and b[off + len(want):] == b"\x07" * (16 - off)
                 assert b[off:off + len(want)] == want, (name, kind, off)
+    sim.close()
+
+
+def test_no_allocation_is_left_unused():
+    """Every device array that grows with the mesh is written by a build and some steps with
+    contact and walls: each is handed out full of one byte, and holds another afterwards."""
+    import torch
+    from paper_2506_05362_amd import pd
+
+    class Marked(Recorder):
+        def __init__(self):
+            super().__init__()
+            self.arrays = {}
+
+            def _alloc(nbytes, user):
+                with torch.cuda.stream(self.stream):
+                    t = torch.full((int(nbytes),), 0xA5, dtype=torch.uint8, device="cuda")
+                self.arrays[t.data_ptr()] = t
+                return t.data_ptr()
+
+            def _free(ptr, user):
+                del self.arrays[ptr]
+
+            self.alloc, self.free = pd.ALLOC_FN(_alloc), pd.FREE_FN(_free)
+
+    wl = _mesh()
+    lo, hi = wl.X.min(axis=1), wl.X.max(axis=1)
+    h = wl.grain_h[0]
+    wl.walls = [I.Wall(normal=(0.0, 0.0, 1.0), offset=lo[2] - 0.5 * h), I.Wall(normal=(0.0, 0.0, -1.0), offset=-hi[2] - 0.5 * h)]
+    mem = Marked()
+    sim = pd.Sim(wl, plumbing=mem)
+    sim.step(25)
+    torch.cuda.synchronize()
+    big = [t for t in mem.arrays.values() if t.numel() >= wl.n_nodes]
+    assert len(big) > 10
+    unused = [t.numel() for t in big if not bool((t != 0xA5).any())]
+    assert not unused, unused
     sim.close()
