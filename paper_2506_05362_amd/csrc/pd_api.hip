@@ -100,8 +100,12 @@ struct pd_ctx {
   int64_t* slice_off = nullptr;
   uint32_t* colE = nullptr;
   uint32_t* colOrig = nullptr;
-  // the step's own rows on the slice path (null: it reads colE, which follows their bond memory)
+  // the step's own rows on the slice path (null: it reads colE), whose bond memory colE
+  // follows when something else reads it
   uint32_t* lined = nullptr;
+  uint64_t* lined_live = nullptr;
+  int16_t* offset_class = nullptr;
+  bool lined_ahead = false;  // steps since colE followed
   bool lined_asked = false;  // made, or found not to be had, since the path was chosen
   int64_t* lined_off = nullptr;
   int32_t* lined_row = nullptr;
@@ -340,6 +344,9 @@ StepArgs step_args(pd_ctx* c) {
   A.lined = c->lined;
   A.lined_off = c->lined_off;
   A.lined_row = c->lined_row;
+  A.lined_live = c->lined_live;
+  A.offset_class = c->offset_class;
+  A.m = c->m;
   A.sentinel_hi = c->sentinel_hi;
   A.intact = c->intact;
   A.self_contact = (c->flags & PD_FLAG_SELF_CONTACT) ? 1 : 0;
@@ -666,7 +673,7 @@ int lattice_order(const pd_ctx* c, int32_t g) {
 }
 
 // For lined rows: axis_order, and on the device the place of every horizon class in rows of each order
-// (stencil: the offsets, packed and lexicographic)
+// and the class of a lattice offset (stencil: the offsets, packed and lexicographic)
 pd_status rank_classes(pd_ctx* c, const std::vector<int32_t>& stencil) {
   c->axis_order.resize((size_t)c->n_grains);
   std::vector<int32_t> order((size_t)c->n_grains);
@@ -686,11 +693,20 @@ pd_status rank_classes(pd_ctx* c, const std::vector<int32_t>& stencil) {
     std::sort(by.begin(), by.end());
     for (size_t k = 0; k < ns; ++k) rank[(size_t)p * ns + (size_t)by[k].second] = (int32_t)k;
   }
+  const int w = 2 * c->m + 1;
+  std::vector<int16_t> at((size_t)w * w * w, -1);
+  for (size_t k = 0; k < ns; ++k) {
+    const int x = (stencil[k] & 255) - 8 + c->m, y = ((stencil[k] >> 8) & 255) - 8 + c->m,
+              z = ((stencil[k] >> 16) & 255) - 8 + c->m;
+    at[((size_t)x * w + y) * w + z] = (int16_t)k;
+  }
   TRY(alloc_n(c, &c->axis_order_d, c->n_grains, "axis orders"));
   TRY(alloc_n(c, &c->axis_rank, (int64_t)rank.size(), "class ranks"));
+  TRY(alloc_n(c, &c->offset_class, (int64_t)at.size(), "classes by offset"));
   hipStream_t s = c->stream;
   HIPCHK(c, hipMemcpyAsync(c->axis_order_d, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice, s));
   HIPCHK(c, hipMemcpyAsync(c->axis_rank, rank.data(), sizeof(int32_t) * rank.size(), hipMemcpyHostToDevice, s));
+  HIPCHK(c, hipMemcpyAsync(c->offset_class, at.data(), sizeof(int16_t) * at.size(), hipMemcpyHostToDevice, s));
   HIPCHK(c, hipStreamSynchronize(s));
   return PD_OK;
 }
@@ -952,6 +968,8 @@ AlignArgs align_args(pd_ctx* c) {
   a.off = c->lined_off;
   a.lined = c->lined;
   a.row = c->lined_row;
+  a.live = c->lined_live;
+  a.sentinel_hi = c->sentinel_hi;
   a.axis_order = c->axis_order_d;
   a.axis_rank = c->axis_rank;
   a.n = c->n;
@@ -965,6 +983,7 @@ void drop_lined(pd_ctx* c) {
   dev_free(c, c->lined);
   dev_free(c, c->lined_off);
   dev_free(c, c->lined_row);
+  dev_free(c, c->lined_live);
   for (int b = 0; b < 2; ++b) {
     dev_free(c, c->uxy[b]);
     dev_free(c, c->uz[b]);
@@ -974,12 +993,16 @@ void drop_lined(pd_ctx* c) {
   c->lined = nullptr;
   c->lined_off = nullptr;
   c->lined_row = nullptr;
+  c->lined_live = nullptr;
+  c->lined_ahead = false;
 }
 
 // what the lined rows and the split copy of u hold, from colE, colOrig and u4
 pd_status fill_lined(pd_ctx* c) {
+  HIPCHK(c, launch_fill_i32(reinterpret_cast<int32_t*>(c->lined_live), 0, 2 * c->nslices * c->n_stencil, c->stream));
   HIPCHK(c, launch_align_fill(align_args(c), c->stream));
   for (int b = 0; b < 2; ++b) HIPCHK(c, launch_split_u(c->u4[b], c->uxy[b], c->uz[b], c->n, c->stream));
+  c->lined_ahead = false;
   return PD_OK;
 }
 
@@ -1008,7 +1031,8 @@ pd_status make_lined(pd_ctx* c) {
     HIPCHK(c, scan_i64(c->lined_off, c->lined_off, c->nslices, scratch, s));
     HIPCHK(c, hipMemcpyAsync(&words, c->lined_off + c->nslices, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
-    ok = words > 0 && get(&c->lined, words) && get(&c->lined_row, words / kWave);
+    ok = words > 0 && get(&c->lined, words) && get(&c->lined_row, words / kWave) &&
+         get(&c->lined_live, c->nslices * c->n_stencil);
     for (int b = 0; b < 2; ++b) ok = ok && get(&c->uxy[b], c->n) && get(&c->uz[b], c->n);
   }
   dev_free(c, scratch);
@@ -1020,10 +1044,14 @@ pd_status make_lined(pd_ctx* c) {
   return fill_lined(c);
 }
 
-// the tile path keeps the bond memory in class masks; bring the column words
-// up to date before anything reads them
+// the tile path keeps the bond memory in class masks, lined rows in their own words;
+// bring the column words up to date before anything reads them
 pd_status sync_columns(pd_ctx* c) {
-  if (c->launch.bond_path != PD_BONDS_TILES) return PD_OK;
+  if (c->launch.bond_path != PD_BONDS_TILES) {
+    if (c->lined_ahead) HIPCHK(c, launch_lined_to_cols(align_args(c), c->stream));
+    c->lined_ahead = false;
+    return PD_OK;
+  }
   StepArgs A = step_args(c);
   HIPCHK(c, launch_mask_to_cols(A, c->ctob, c->colOrig, c->stream));
   return PD_OK;
@@ -1563,6 +1591,7 @@ pd_status pd_step(pd_ctx* c, int64_t n_steps) {
   if (!c->built) return fail(c, PD_ERR_STATE, "pd_build_bonds must come first");
   if (n_steps < 0) return fail(c, PD_ERR_INVALID, "n_steps < 0");
   if (n_steps > 0) TRY(make_lined(c));
+  if (n_steps > 0 && c->lined) c->lined_ahead = true;
   int64_t left = n_steps;
   const int64_t step0 = c->step;
   const bool watch = early_rebuilds(c);
@@ -1637,12 +1666,16 @@ pd_status pd_set_launch(pd_ctx* c, const pd_launch* l) {
   }
   TRY(drop_graphs(c));
   if (c->built && l->bond_path != c->launch.bond_path) {
-    // hand the bond memory over: column words <-> class masks
+    // hand the bond memory over: lined rows -> column words <-> class masks
+    TRY(sync_columns(c));
     if (l->bond_path == PD_BONDS_TILES) HIPCHK(c, launch_cols_to_mask(step_args(c), c->ctob, c->colOrig, c->stream));
-    else TRY(sync_columns(c));
     HIPCHK(c, hipStreamSynchronize(c->stream));
   }
   if (!lines_rows(*l)) {
+    if (c->lined_ahead) {
+      TRY(sync_columns(c));
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+    }
     drop_lined(c);
     c->lined_asked = false;
   }

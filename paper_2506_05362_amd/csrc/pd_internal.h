@@ -166,11 +166,15 @@ struct StepArgs {
   const int64_t* slice_off;
   const int32_t* rowlen;
   uint32_t* colE;           // live column words; a broken bond becomes node_i | sentinel_hi
-  // the rows with classes lined up (null: the steps read colE), their slice offsets and
-  // the byte offset of each entry's row in the stencil tables
+  // the rows with classes lined up (null: the steps read colE), which then hold the bond
+  // memory of the slices that have them, their slice offsets and the byte offset of each
+  // entry's row in the stencil tables
   uint32_t* lined;
   const int64_t* lined_off;
   const int32_t* lined_row;
+  uint64_t* lined_live;         // see AlignArgs
+  const int16_t* offset_class;  // [(2 m + 1)^3] class of a lattice offset, -1 beyond the horizon
+  int32_t m;
   int32_t* intact;
   const int32_t* cand_ptr;
   const int32_t* cand;
@@ -268,18 +272,19 @@ struct AlignArgs {
   const GrainC* grains;
   const int32_t* rowlen;
   const int64_t* slice_off;
-  const uint32_t* colE;
+  uint32_t* colE;
   const uint32_t* colOrig;
   int64_t* off;     // [nslices + 1]
   uint32_t* lined;  // column words: node, with kBroken set where there is no bond (any more)
   int32_t* row;     // [off[nslices] / 64]
+  uint64_t* live;   // [nslices][n_stencil] lanes whose bond of a class is intact
+  uint32_t sentinel_hi;
   int64_t n, nslices;
   const int32_t* axis_order;  // [G] axis order of the grain's node list
   const int32_t* axis_rank;   // [6][n_stencil] place of a class in rows of that order
   int32_t n_stencil, node_bits;
 };
-// flags of a lined word, above any node index: no bond; one that broke in this pass
-constexpr uint32_t kBroken = 1u << 31, kFresh = 1u << 30;
+constexpr uint32_t kBroken = 1u << 31;  // a lined word, above any node index: no bond
 constexpr int64_t kLinedNodes = (int64_t)1 << 28;  // byte offsets of (x, y) pairs in 32 bits
 // Lined rows pay from four slices for each of 1024 SIMDs, whose wavefronts then hide each
 // other's waits for scalar loads.  Lined / compact, us a launch: 1,964 slices 48 / 42,
@@ -338,6 +343,8 @@ hipError_t launch_slice_width(const BuildArgs& b, hipStream_t s);
 hipError_t launch_bond_fill(const BuildArgs& b, hipStream_t s);
 hipError_t launch_align_width(const AlignArgs& a, hipStream_t s);
 hipError_t launch_align_fill(const AlignArgs& a, hipStream_t s);
+// breaks in the lined rows into the column words
+hipError_t launch_lined_to_cols(const AlignArgs& a, hipStream_t s);
 hipError_t launch_step(const StepArgs& a, int mode, hipStream_t s);
 // corner corrections of this evaluation (before the step kernel)
 hipError_t launch_wall_corners(const StepArgs& a, int force_only, hipStream_t s);

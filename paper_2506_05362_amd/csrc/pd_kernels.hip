@@ -13,9 +13,11 @@
 //            lattice offset in the horizon stencil.  Bond memory lives in the
 //            word itself: a bond that breaks is rewritten to node_i with the
 //            zero-force class, which is also what padding entries hold, so the
-//            step kernel needs no separate broken-flag reads.  The slice path's steps
-//            read a second set of rows, in which the lanes of a slice hold the
-//            same class at the same entry (k_align), and write breaks to both.
+//            step kernel needs no separate broken-flag reads.  On large meshes
+//            the slice path's steps read, and break bonds in, a second set of
+//            rows, in which the lanes of a slice hold the same class at the same
+//            entry (k_align); the column words follow when something else reads
+//            them (k_lined_to_cols).
 //
 // Each lane owns one node and evaluates its row in order (gather formulation,
 // Sec. 3.1 eq. (peri-damage) with nodal quadrature, Sec. 6.1): no atomics, so
@@ -296,6 +298,10 @@ __global__ __launch_bounds__(kBlock) void k_align(AlignArgs a) {
       const uint32_t j = (uint32_t)__shfl((int)(w & node_mask), src, kWave);
       out[(int64_t)p * kWave] = take && l == w ? j : j | kBroken;
       if (take) row[p] = (int32_t)((table + (w >> a.node_bits)) * (uint32_t)sizeof(StencilC));  // (all the same)
+      // (entries of several tables share a class's mask, zero before)
+      const uint64_t intact = __ballot(take && l == w);
+      if (lane == __ffsll((unsigned long long)has) - 1)
+        atomicOr((unsigned long long*)(a.live + s * a.n_stencil + (w >> a.node_bits)), (unsigned long long)intact);
     }
     if (take) {
       ++k;
@@ -311,6 +317,21 @@ __global__ __launch_bounds__(kBlock) void k_align(AlignArgs a) {
     }
   } else if (lane == 0) {
     a.off[s] = p > limit ? 0 : (int64_t)((p + kBatch - 1) / kBatch * kBatch) * kWave;
+  }
+}
+
+// the column words of the slices with lined rows: an entry whose lane bit is clear becomes
+// a broken one
+__global__ void k_lined_to_cols(AlignArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  const int64_t s = i / kWave, lane = i % kWave;
+  if (a.off[s + 1] == a.off[s]) return;
+  for (int k = 0; k < a.rowlen[i]; ++k) {
+    const int64_t at = a.slice_off[s] + (int64_t)k * kWave + lane;
+    const uint32_t wo = a.colOrig[at];
+    const bool intact = (a.live[s * a.n_stencil + (wo >> a.node_bits)] >> lane) & 1ull;
+    a.colE[at] = intact ? wo : (uint32_t)i | a.sentinel_hi;
   }
 }
 
@@ -598,9 +619,15 @@ __device__ __forceinline__ NodeVA load_va(const StepArgs& A, int64_t i, bool val
   return r;
 }
 
-// The entry of the bond from node i to node j in the compact rows, -1 if there is
-// none: the node's entries as built are sorted by neighbour index.
-__device__ __forceinline__ int64_t bond_entry(const StepArgs& A, int64_t i, int j) {
+// Is the bond from node i to node j (same grain) intact after this evaluation's
+// breaks?  The node's built entries are sorted by neighbour index, so a binary
+// search finds j's entry; a pair with no entry (outside the horizon, or cut)
+// has no bond.  The bond memory is the live column word on the compact rows
+// (path = kInCols) and, on the tiled path, the node's lane bit in the lane mask of
+// its class in the grain's axis order path (the tile kernel stores a class's
+// mask as soon as a bond of it breaks, before any node's tail).
+constexpr int kInCols = -1, kInLined = -2;
+__device__ __forceinline__ bool bond_intact(const StepArgs& A, int64_t i, int j, int path) {
   const uint32_t node_mask = (1u << A.node_bits) - 1u;
   const int64_t base = A.slice_off[i >> 6] + (i & 63);
   int lo = 0, hi = A.rowlen[i] - 1;
@@ -614,26 +641,26 @@ __device__ __forceinline__ int64_t bond_entry(const StepArgs& A, int64_t i, int 
     } else if (jm > j) {
       hi = mid - 1;
     } else {
-      return at;
+      if (path < 0) return A.colE[at] == wo;
+      const int b = A.ctob[path * A.n_stencil + (int)(wo >> A.node_bits)];
+      const int32_t sl = A.slot[i];
+      return ((A.lmask[(int64_t)(sl >> 6) * kTileClasses + b] >> (sl & 63)) & 1ull) != 0ull;
     }
   }
-  return -1;
+  return false;
 }
 
-// Is the bond from node i to node j (same grain) intact after this evaluation's
-// breaks?  A pair with no entry (outside the horizon, or cut) has no bond.  The
-// bond memory is the live column word on the slice path
-// (perm < 0) and, on the tiled path, the node's lane bit in the lane mask of
-// its class in the grain's axis order perm (the tile kernel stores a class's
-// mask as soon as a bond of it breaks, before any node's tail).
-__device__ __forceinline__ bool bond_intact(const StepArgs& A, int64_t i, int j, int perm) {
-  const int64_t at = bond_entry(A, i, j);
-  if (at < 0) return false;
-  const uint32_t wo = A.colOrig[at];
-  if (perm < 0) return A.colE[at] == wo;
-  const int b = A.ctob[perm * A.n_stencil + (int)(wo >> A.node_bits)];
-  const int32_t sl = A.slot[i];
-  return ((A.lmask[(int64_t)(sl >> 6) * kTileClasses + b] >> (sl & 63)) & 1ull) != 0ull;
+// The same for a slice with lined rows: the lattice offset from pi to pj (packed) names the
+// class, whose lane mask of intact bonds the slice keeps.  (The bond loop takes breaks
+// from the masks by atomics; the load is one as well, past the first-level cache.)
+__device__ __forceinline__ bool bond_intact_lined(const StepArgs& A, int64_t i, int pi, int pj) {
+  const int m = A.m, w = 2 * m + 1;
+  const int x = unpack_x(pj) - unpack_x(pi) + m, y = unpack_y(pj) - unpack_y(pi) + m, z = unpack_z(pj) - unpack_z(pi) + m;
+  if (min(min(x, y), z) < 0 || max(max(x, y), z) >= w) return false;
+  const int k = A.offset_class[(x * w + y) * w + z];
+  if (k < 0) return false;
+  const uint64_t live = __hip_atomic_load(A.lined_live + (i >> 6) * A.n_stencil + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (live >> (i & 63)) & 1ull;
 }
 
 // Repulsion of node j on node i when closer than R_c (Sec. 3.2), with normal
@@ -646,12 +673,13 @@ template <bool EXTRA>
 __device__ __forceinline__ void contact_pair(const StepArgs& A, int64_t i, int j, bool listed, const double4& uj,
                                              const double4& Xj, const double4& Xi, const double4& ui,
                                              const double4& vhi, int mi, double rho_i, bool damp, bool fric,
-                                             int perm, double& fx, double& fy, double& fz) {
+                                             int path, double& fx, double& fy, double& fz) {
   double yx, yy, yz;
   const double d2 = contact_d2(Xj.x, Xi.x, uj.x, ui.x, Xj.y, Xi.y, uj.y, ui.y, Xj.z, Xi.z, uj.z, ui.z, yx, yy, yz);
   if (listed && d2 < A.Rc2 && d2 > 0.0) {
     // a node of the same grain repels only while no intact bond joins the two
-    if (EXTRA && A.self_contact && packed_grain(uj.w) == packed_grain(ui.w) && bond_intact(A, i, j, perm))
+    if (EXTRA && A.self_contact && packed_grain(uj.w) == packed_grain(ui.w) &&
+        (path == kInLined ? bond_intact_lined(A, i, packed_ijk(ui.w), packed_ijk(uj.w)) : bond_intact(A, i, j, path)))
       return;
     // where all grains are alike their constants are kernel arguments, not loads
     // behind the partner's
@@ -727,7 +755,7 @@ template <int MODE, bool EXTRA, bool SCALAR_WALLS, bool SPLIT>
 __device__ __forceinline__ void node_tail(const StepArgs& A, int64_t i, bool valid, const double4& ui,
                                           const GrainC* G, int ix, int iy, int iz, double fx, double fy,
                                           double fz, int nbroke, bool col_ok, int64_t col, const NodeVA& va,
-                                          int perm) {
+                                          int path) {
   const int lane = threadIdx.x & 63;
   // mid-step velocity of this node for the normal damping (Sec. 3.4) and
   // stick-slip friction (Sec. 3.3) laws
@@ -778,7 +806,7 @@ __device__ __forceinline__ void node_tail(const StepArgs& A, int64_t i, bool val
         }
 #pragma unroll
         for (int k = 0; k < kContactBatch; ++k)
-          contact_pair<EXTRA>(A, i, jj[k], e + k < c1, uj[k], Xj[k], Xi, ui, vhi, mi, own.rho, damp, fric, perm, fx,
+          contact_pair<EXTRA>(A, i, jj[k], e + k < c1, uj[k], Xj[k], Xi, ui, vhi, mi, own.rho, damp, fric, path, fx,
                               fy, fz);
       }
     }
@@ -1072,6 +1100,10 @@ __device__ __forceinline__ bool lined_up(const StepArgs& A, int64_t slice) {
 // that a line holds four and eight nodes instead of two: 66 instead of 78; lanes
 // without the bond reading a neighbour's line: 60 instead of 66).  523,690 nodes in 125
 // spheres: 149 us a launch instead of 204.
+// A break is one store and, for the wavefront, one atomic on the class's mask; the compact
+// rows follow when something reads them.  Written to both by the step, through a search of
+// the compact row, the breaks of a collision at 50 m/s (274,130 nodes) took a step from 110
+// to 170 us (compact rows 121, now 92 to 101).
 template <int MODE, bool ABS, int DEPTH>
 __device__ __forceinline__ void bonds_lined(const StepArgs& A, int64_t slice, int64_t i, int lane, bool valid,
                                             const double4& ui, const GrainC* G, double& fx, double& fy,
@@ -1162,9 +1194,14 @@ __device__ __forceinline__ void bonds_lined(const StepArgs& A, int64_t slice, in
       add_on_lanes(live & ~ov, coef, yx, yy, yz, fx, fy, fz);
       if (__builtin_expect(MODE != MODE_FORCE_ONLY && (live & ov & mine) != 0ull, 0)) {
         if (over && valid && (int32_t)c[u] >= 0) {
-          cp[(b * kBatch + u) * kWave] = c[u] | kBroken | kFresh;  // the bond stays broken from now on
+          cp[(b * kBatch + u) * kWave] = c[u] | kBroken;  // the bond stays broken from now on
           ++nbroke;
         }
+        // and in its class's mask, by atomics: lanes of another table share it
+        const uint32_t k = (uint32_t)rc[u] / (uint32_t)sizeof(StencilC) % (uint32_t)(A.n_stencil + 1);
+        if (lane == 0)
+          __hip_atomic_fetch_and(A.lined_live + slice * A.n_stencil + k, ~(live & ov & mine), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   };
@@ -1179,17 +1216,6 @@ __device__ __forceinline__ void bonds_lined(const StepArgs& A, int64_t slice, in
       columns(b0 + r + CR - 1, cw[(r + CR - 1) % CR]);
       gather(cw[(r + DEPTH - 1) % CR], (r + DEPTH - 1) % DEPTH);
       batch(b0 + r, cw[r], r % DEPTH);
-    }
-  }
-  // the compact rows follow
-  if (MODE != MODE_FORCE_ONLY && __ballot(nbroke > 0) != 0ull) {
-    if (nbroke > 0) {
-      for (int p = 0; p < W; ++p) {
-        const uint32_t w = cp[(int64_t)p * kWave];
-        if (!(w & kFresh)) continue;
-        A.colE[bond_entry(A, i, (int)(w & ~(kBroken | kFresh)))] = (uint32_t)i | A.sentinel_hi;
-        cp[(int64_t)p * kWave] = w & ~kFresh;
-      }
     }
   }
 }
@@ -1209,12 +1235,14 @@ __device__ __forceinline__ void step_body(const StepArgs& A, const StencilC* s_s
   const GrainC* G = A.grains + (valid ? packed_grain(ui.w) : 0);
   double fx = 0.0, fy = 0.0, fz = 0.0;
   int nbroke = 0;
-  if (LINED && slice_ok && lined_up(A, slice))
+  const bool lined = LINED && slice_ok && lined_up(A, slice);
+  if (lined)
     bonds_lined<MODE, ABS, DEPTH>(A, slice, i, lane, valid, ui, G, fx, fy, fz, nbroke);
   else
     bonds_compact<MODE, ABS, DEPTH>(A, s_st, slice, slice_ok, i, lane, valid, ui, G, fx, fy, fz, nbroke);
   node_tail<MODE, true, SCALAR_WALLS, LINED>(A, i, valid, ui, G, unpack_x(pi), unpack_y(pi), unpack_z(pi), fx, fy, fz, nbroke,
-                                      slice_ok, A.partial_base + (slice - A.slice_base), load_va(A, i, valid), -1);
+                                      slice_ok, A.partial_base + (slice - A.slice_base), load_va(A, i, valid),
+                                      lined ? kInLined : kInCols);
 }
 
 __device__ __forceinline__ void stage_stencil(const StepArgs& A, StencilC* s_st) {
@@ -2737,6 +2765,12 @@ hipError_t launch_align_width(const AlignArgs& a, hipStream_t s) {
 hipError_t launch_align_fill(const AlignArgs& a, hipStream_t s) {
   if (a.nslices == 0) return hipSuccess;
   hipLaunchKernelGGL(k_align<true>, dim3(grid_for(a.nslices, kSlicesPerBlock)), dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_lined_to_cols(const AlignArgs& a, hipStream_t s) {
+  if (a.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_lined_to_cols, dim3(grid_for(a.n, 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
