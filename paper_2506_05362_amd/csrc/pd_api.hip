@@ -915,8 +915,6 @@ pd_status build_tiles(pd_ctx* c) {
         const int q = tile_norm(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
         tn.bond[q][0] = r.inv_l0sq;
         tn.bond[q][1] = r.civ;
-        tn.l0[q] = r.l0;
-        tn.l0sq[q] = r.l0sq;
         if (d[0] > 0 && d[1] == 0 && d[2] == 0) tn.h[d[0]] = r.hx;
       }
       for (const GrainC& gc : c->grains_h)
@@ -1257,10 +1255,10 @@ pd_status pd_init(pd_ctx** out, const pd_grains* grains, const pd_mesh* mesh,
       const double l0 = h * sqrt(d2), l0sq = h * h * d2;
       // micromodulus weight: 1, or 1 - |xi|/delta for the conic form
       const double w = (P.flags & PD_FLAG_CONIC) ? 1.0 - l0 / (P.horizon_factor * h) : 1.0;
-      st.push_back(StencilC{h * sd[3 * k], h * sd[3 * k + 1], h * sd[3 * k + 2], 1.0 / l0sq, cV * w / l0, l0, l0sq});
+      st.push_back(StencilC{h * sd[3 * k], h * sd[3 * k + 1], h * sd[3 * k + 2], 1.0 / l0sq, cV * w / l0});
     }
     // zero-force class: xi = 0, x = 0, c V / |xi| = 0 (broken bonds, padding)
-    st.push_back(StencilC{0.0, 0.0, 0.0, 0.0, 0.0, 1.0, 1.0});
+    st.push_back(StencilC{0.0, 0.0, 0.0, 0.0, 0.0});
   }
   c->stencil_h = st;
   c->sd_h = sd;

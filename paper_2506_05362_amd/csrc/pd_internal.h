@@ -49,13 +49,12 @@ struct GrainOne {
 
 // One row per horizon-stencil offset d (lexicographic order) and per
 // (h, material) class, with every constant of the bond law folded in:
-// xi = h d, 1/|xi|^2, c V / |xi|, and for the exact form |xi|, |xi|^2.  The row
-// after the last offset is the zero-force class of broken bonds and padding.
+// xi = h d, 1/|xi|^2 and c V / |xi|.  The row after the last offset is the
+// zero-force class of broken bonds and padding.
 struct StencilC {
   double hx, hy, hz;  // xi
   double inv_l0sq;    // 1 / |xi|^2
   double civ;         // c V / |xi|
-  double l0, l0sq;    // |xi|, |xi|^2
 };
 constexpr int kTableRow = 64;  // bytes of a row counted against the tables' space
 constexpr int kMaxLdsTables = 48 * 1024;  // bytes of stencil tables a workgroup may stage
@@ -93,7 +92,6 @@ struct TileNorms {
   double h[4];  // 0, h, 2 h, 3 h
   double thr_x, lo_x;
   double bond[kTileNorms][2];  // 1 / |xi|^2, c V / |xi|
-  double l0[kTileNorms], l0sq[kTileNorms];
 };
 
 // A tile box: a grain's own lattice box, or (lattice mode) one box over every

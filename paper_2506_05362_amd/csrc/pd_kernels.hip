@@ -359,22 +359,20 @@ __device__ __forceinline__ double wave_sum(double x) {
 #define PD_STEP_WAVES_PER_EU 4
 #endif
 
-// 1 - (1 + x)^(-1/2) = x q(x).  q is a polynomial (coefficients from
-// csrc/bond_series.py), constant term exactly 1/2: degree 6 for |x| <= kShortRange
-// (stretches up to 0.27%, beyond the critical stretch of sand at the sizes meshed
-// here, 0.17%), degree 8 up to kPolyRange, both with relative errors of about
-// 1e-18; beyond, the exact form.
-constexpr double kShortRange = 0.0055, kPolyRange = 0.02;
-// The non-trivial coefficients, highest degree first.  The tile kernel holds the
-// short polynomial's in scalar registers, with the same arithmetic either way: as
+// g = 1 - (1 + x)^(-1/2) = x q(x).  For |x| <= kShortRange (stretches up to 0.27%, beyond the
+// critical stretch of sand at the sizes meshed here, 0.17%) q is a polynomial of degree 6
+// (coefficients from csrc/bond_series.py, constant term exactly 1/2, relative error about
+// 1e-18).  Up to kWideRange the same polynomial's value, by then off by up to 9e-9, is
+// corrected once (g_corrected); beyond, the exact form.
+constexpr double kShortRange = 0.0055, kWideRange = 0.08;
+// The non-trivial coefficients, highest degree first.  The tile kernel holds them in
+// scalar registers, with the same arithmetic either way: as
 // literals the compiler rebuilds each 64-bit constant with two moves per use.
 struct PolyS {
   double c[6];
 };
 constexpr PolyS kPolyS{{0x1.ad0525d77783ap-3, -0x1.ce05735c7b7b0p-3, 0x1.f7fffffae5b32p-3, -0x1.17fffffd4c6e0p-2,
                          0x1.400000000000ap-2, -0x1.800000000000bp-2}};
-constexpr double kPolyL[8] = {0x1.7c2767adf6933p-3, -0x1.92832f94213d7p-3, 0x1.acfff9e68ffc4p-3, -0x1.cdfff99c37884p-3,
-                              0x1.f80000002c6aep-3, -0x1.1800000017442p-2, 0x1.3fffffffffffdp-2, -0x1.7fffffffffffdp-2};
 __device__ __forceinline__ double q_short(double x, const PolyS& P) {
   double p = fma(P.c[0], x, P.c[1]);
 #pragma unroll
@@ -388,17 +386,26 @@ __device__ __forceinline__ PolyS poly_in_registers() {
   for (int k = 1; k < 6; ++k) asm volatile("" : "+s"(P.c[k]));
   return P;
 }
-// a constant of the rarely taken forms, made where it is used: hoisted out of the
-// bond loops, all of them together would hold some thirty vector registers
-__device__ __forceinline__ double rare_const(double c) {
-  asm volatile("" : "+s"(c));
-  return c;
+// One Newton step of r = 1 - g towards (1 + x)^(-1/2): with e = 1 - (1 + x) r^2, r (1 + e/2).
+// e = (2 g - x) + g (2 x - g - x g), whose first difference is exact, so that g comes out
+// right to half a unit in the last place (the error left, 3/8 e^2, is 5e-18 of g at |x| =
+// 0.08).  Six operations and no constants to make, where a polynomial of degree 8 (up to
+// 0.02) took nine and sixteen scalar moves, 122 times over in the tile kernel: what a
+// strained body fetched did not fit the instruction cache.  Random displacements of 0.6% of
+// a spacing, 274,130 nodes: tiles 87 us a step instead of 117, lined rows 84 instead of
+// 118; compact rows (48,900 nodes) 43 instead of 59; calm bodies as before.
+__device__ __forceinline__ double g_corrected(double x, double q) {
+  double g = x * q;
+  asm volatile("" : "+v"(g));  // (keeps this where it is rarely taken, out of the straight code)
+  const double e = fma(g, fma(-x, g, fma(2.0, x, -g)), fma(2.0, g, -x));
+  return fma(e, fma(0.5, g, -0.5), g);
 }
-__device__ __forceinline__ double q_long(double x) {
-  double p = fma(rare_const(kPolyL[0]), x, rare_const(kPolyL[1]));
-#pragma unroll
-  for (int k = 2; k < 8; ++k) p = fma(p, x, rare_const(kPolyL[k]));
-  return fma(p, x, 0.5);
+
+// The exact form, x / (w + sqrt(w)) with w = 1 + x taken as |y|^2 / |xi|^2: right to 6e-16
+// also where a bond is compressed to a fraction of its length and 1 + x would cancel.
+__device__ __forceinline__ double g_exact(double x, double yx, double yy, double yz, double inv) {
+  const double w = fma(yx, yx, fma(yy, yy, yz * yz)) * inv;
+  return x * rcp_full(fma(w, rsqrt_full(w), w));
 }
 
 // The fused step of one workgroup: SPB slices (one wavefront each) starting at
@@ -945,14 +952,6 @@ __device__ __forceinline__ void node_tail(const StepArgs& A, int64_t i, bool val
   }
 }
 
-// the bond force beyond the short polynomial's range, over y
-__device__ __forceinline__ double far_coef(const StencilC& S, double d, double x) {
-  const double lsq = S.l0sq + d;
-  const double l = lsq * rsqrt_full(lsq);
-  const double ce = S.civ * (d * rcp_full(fma(l, S.l0, lsq)));
-  return fabs(x) <= kPolyRange ? (S.civ * x) * q_long(x) : ce;
-}
-
 // The bond sum of a slice over the compact rows, their tables in LDS.
 template <int MODE, bool ABS, int DEPTH>
 __device__ __forceinline__ void bonds_compact(const StepArgs& A, const StencilC* s_st, int64_t slice, bool slice_ok,
@@ -977,9 +976,9 @@ __device__ __forceinline__ void bonds_compact(const StepArgs& A, const StencilC*
   // Bond law (Sec. 3.1): the force on i is c s V_j y/|y|, y = xi + eta, and
   //   c V s / |y| = (c V / |xi|) g,   g = 1 - |xi|/|y| = 1 - (1 + x)^(-1/2),
   //   x = (|y|^2 - |xi|^2) / |xi|^2,   |y|^2 - |xi|^2 = eta . (2 xi + eta).
-  // g comes from a polynomial when |x| <= kPolyRange (no square root or
-  // division), else from g = (|y|^2 - |xi|^2) / (|y| (|y| + |xi|)); neither form
-  // subtracts nearly equal numbers.  The bond breaks when s > s0, which is x >
+  // g comes from a polynomial, corrected past kShortRange, when |x| <= kWideRange (no
+  // square root or division), else from g = (|y|^2 - |xi|^2) / (|y| (|y| + |xi|)), over
+  // |xi|^2; no form subtracts nearly equal numbers.  The bond breaks when s > s0, which is x >
   // (1 + s0)^2 - 1.  The form is chosen per lane, so any grouping of bonds (the
   // tiled path) computes the same values.
   int64_t off = 0;
@@ -1028,11 +1027,15 @@ __device__ __forceinline__ void bonds_compact(const StepArgs& A, const StencilC*
       const double x = d * S.inv_l0sq;
       bool over = x > thr_x;
       if (ABS) over = over || x < lo_x;
-      double coef = (S.civ * x) * q_short(x, P);
+      const double q = q_short(x, P);
+      double coef = (S.civ * x) * q;
       const bool far = !(fabs(x) <= kShortRange);
-      if (__builtin_expect(__ballot(far) != 0ull, 0))
-        coef = far ? far_coef(*reinterpret_cast<const StencilC*>(tbase + (c[u] >> node_bits) * (uint32_t)sizeof(StencilC)), d, x)
-                   : coef;
+      if (__builtin_expect(__ballot(far) != 0ull, 0)) {
+        const bool exact = !(fabs(x) <= kWideRange);
+        double g = g_corrected(x, q);
+        if (__builtin_expect(__ballot(exact) != 0ull, 0)) g = exact ? g_exact(x, yx, yy, yz, S.inv_l0sq) : g;
+        coef = far ? S.civ * g : coef;
+      }
       coef = over ? 0.0 : coef;
       fx = fma(coef, yx, fx);
       fy = fma(coef, yy, fy);
@@ -1173,22 +1176,17 @@ __device__ __forceinline__ void bonds_lined(const StepArgs& A, int64_t slice, in
       const double x = d * S.inv;
       bool over = x > thr_x;
       if (ABS) over = over || x < lo_x;
-      const double civ = S.civ, cx = civ * x;
+      const double inv = S.inv, civ = S.civ, cx = civ * x;
       S = row_at(u + 1 < kBatch ? rc[(u + 1) % kBatch] : rn[0]);
-      double coef = cx * q_short(x, P);
+      const double q = q_short(x, P);
+      double coef = cx * q;
       const uint64_t live = __ballot((int32_t)c[u] >= 0);
       const bool far = !(fabs(x) <= kShortRange);
       if (__builtin_expect((__ballot(far) & live) != 0ull, 0)) {
-        const bool exact = !(fabs(x) <= kPolyRange);
-        double cl = cx * q_long(x);
-        if (__builtin_expect((__ballot(exact) & live) != 0ull, 0)) {
-          const TileTab t = (TileTab)(tbase + rc[u]);
-          const double lsq = t->l0sq + d;
-          const double l = lsq * rsqrt_full(lsq);
-          const double ce = civ * (d * rcp_full(fma(l, t->l0, lsq)));
-          cl = exact ? ce : cl;
-        }
-        coef = far ? cl : coef;
+        const bool exact = !(fabs(x) <= kWideRange);
+        double g = g_corrected(x, q);
+        if (__builtin_expect((__ballot(exact) & live) != 0ull, 0)) g = exact ? g_exact(x, yx, yy, yz, inv) : g;
+        coef = far ? civ * g : coef;
       }
       const uint64_t ov = __ballot(over);
       add_on_lanes(live & ~ov, coef, yx, yy, yz, fx, fy, fz);
@@ -1409,33 +1407,28 @@ __device__ __forceinline__ double plus_xi(double e, const TileK& T) {
 // launch took 143 us instead of 117, the large aggregate's 1927 us instead of 1780.
 // The other forms and the breaks are marked unlikely: placed out of line, so that the
 // straight code of 122 classes fits the instruction cache (plate 117.9 -> 115.5 us,
-// a volume of 373,248 nodes 84.1 -> 77.2, the large aggregate 1621 -> 1548).
+// a volume of 373,248 nodes 84.1 -> 77.2, the large aggregate 1621 -> 1548), and short
+// (see g_corrected).
 template <int K, bool ABS, int PERM>
 __device__ __forceinline__ void tile_bond(const double* L, const double* Lz, const StencilC* tabp, const TileNorms* norms,
                                           const uint64_t* mrow, uint64_t* mrow_w, TileIn& in, const TileK& T,
                                           double uix, double uiy, double uiz, int& nbroke, double& fx, double& fy,
                                           double& fz) {
-  constexpr int N = tile_class(K).norm;
   const double ex = in.ux - uix, ey = in.uy - uiy, ez = in.uz - uiz;
-  double yx, yy, yz, wx, wy, wz;  // xi + eta, 2 xi + eta
+  constexpr int cx = tile_comp(K, PERM < 0 ? 0 : PERM, 0), cy = tile_comp(K, PERM < 0 ? 0 : PERM, 1),
+                cz = tile_comp(K, PERM < 0 ? 0 : PERM, 2);
+  double wx, wy, wz;  // 2 xi + eta
   if constexpr (PERM >= 0) {
-    constexpr int cx = tile_comp(K, PERM, 0), cy = tile_comp(K, PERM, 1), cz = tile_comp(K, PERM, 2);
-    yx = plus_xi<cx, 1>(ex, T);
-    yy = plus_xi<cy, 1>(ey, T);
-    yz = plus_xi<cz, 1>(ez, T);
     wx = plus_xi<cx, 2>(ex, T);
     wy = plus_xi<cy, 2>(ey, T);
     wz = plus_xi<cz, 2>(ez, T);
   } else {
-    yx = in.hx + ex;
-    yy = in.hy + ey;
-    yz = in.hz + ez;
     wx = fma(2.0, in.hx, ex);
     wy = fma(2.0, in.hy, ey);
     wz = fma(2.0, in.hz, ez);
   }
   const uint64_t live = in.live[K % kMaskGroup];
-  const double inv = in.inv, civ = in.civ;
+  const double inv = in.inv, civ = in.civ, hx = in.hx, hy = in.hy, hz = in.hz;
   __builtin_amdgcn_sched_barrier(0);
   if constexpr ((K + 1) % kMaskGroup == 0) {
 #pragma unroll
@@ -1443,25 +1436,41 @@ __device__ __forceinline__ void tile_bond(const double* L, const double* Lz, con
     mask_load<(K + 1) / kMaskGroup + 1>(mrow, in.next);
   }
   if constexpr (K + 1 < kTileClasses) tile_load<K + 1, PERM>(L, Lz, tabp, norms, in);
+  auto xi_plus = [&](double ax, double ay, double az, double& yx, double& yy, double& yz) {
+    if constexpr (PERM >= 0) {
+      yx = plus_xi<cx, 1>(ax, T);
+      yy = plus_xi<cy, 1>(ay, T);
+      yz = plus_xi<cz, 1>(az, T);
+    } else {
+      yx = hx + ax;
+      yy = hy + ay;
+      yz = hz + az;
+    }
+  };
+  double yx, yy, yz;  // xi + eta
+  xi_plus(ex, ey, ez, yx, yy, yz);
   const double d = fma(ex, wx, fma(ey, wy, ez * wz));
   const double x = d * inv;
   bool over = x > T.thr_x;
   if (ABS) over = over || x < T.lo_x;
   const double cx_ = civ * x;
-  double coef = cx_ * q_short(x, T.P);
+  const double q = q_short(x, T.P);
+  double coef = cx_ * q;
   // the per-lane choice of the slice path, the other forms computed only when a
   // lane with an intact bond needs them
   const bool far = !(fabs(x) <= kShortRange);
   if (__builtin_expect((__ballot(far) & live) != 0ull, 0)) {
-    const bool exact = !(fabs(x) <= kPolyRange);
-    double cl = cx_ * q_long(x);
+    const bool exact = !(fabs(x) <= kWideRange);
+    double g = g_corrected(x, q);
     if (__builtin_expect((__ballot(exact) & live) != 0ull, 0)) {
-      const double lsq = ((NormTab)norms)->l0sq[N] + d;
-      const double l = lsq * rsqrt_full(lsq);
-      const double ce = civ * (d * rcp_full(fma(l, ((NormTab)norms)->l0[N], lsq)));
-      cl = exact ? ce : cl;
+      // (y made here again: used by both, it would be made before the break test, whose
+      // latency it covers where it is: 1% of the launch)
+      double ax = ex, ay = ey, az = ez, bx, by, bz;
+      asm volatile("" : "+v"(ax), "+v"(ay), "+v"(az));
+      xi_plus(ax, ay, az, bx, by, bz);
+      g = exact ? g_exact(x, bx, by, bz, inv) : g;
     }
-    coef = far ? cl : coef;
+    coef = far ? civ * g : coef;
   }
   // an intact bond within its limit adds its force; a bond past its limit stays
   // broken from now on
@@ -1469,9 +1478,9 @@ __device__ __forceinline__ void tile_bond(const double* L, const double* Lz, con
   add_on_lanes(live & ~ov, coef, yx, yy, yz, fx, fy, fz);
   const uint64_t brk = live & ov;
   if (__builtin_expect(brk != 0ull, 0)) {
-    const int lane = __lane_id();
-    if (lane == 0) mrow_w[K] = live & ~ov;
-    nbroke += (int)((brk >> lane) & 1ull);
+    uint64_t carry;
+    mrow_w[K] = live & ~ov;  // (by every lane, the same)
+    asm("v_addc_co_u32_e64 %0, %1, %0, 0, %2" : "+v"(nbroke), "=&s"(carry) : "s"(brk));
   }
 }
 
