@@ -292,13 +292,14 @@ __device__ __forceinline__ void wgrad_bias(const WGrad& L, int n0, int64_t batch
     for (int d = 0; d < kBD; ++d) {
       const int64_t b0 = c0 + d * kWK;
       const int buf = d & 1;
+      if (masked && b0 >= batch) return;  // (the same for the workgroup)
       if (masked) x[d].mask(b0, batch);
 #pragma unroll
       for (int g = 0; g < R::kBlocks; ++g)
 #pragma unroll
         for (int k = 0; k < 4; ++k) *reinterpret_cast<v4f*>(&s[buf][R::col() + k][R::row(g)]) = x[d].column(g, k);
       __syncthreads();  // the other buffer was read before this barrier's arrival
-      x[d].load(L.dZ, L.ldz, n0, b0 + kBD * kWK, batch);
+      if (!masked) x[d].load(L.dZ, L.ldz, n0, b0 + kBD * kWK, batch);
       if (threadIdx.x < kBT) {
 #pragma unroll
         for (int r = 0; r < kWK; r += 4) {
@@ -333,6 +334,7 @@ __device__ __forceinline__ void wgrad_tile(const WGrad& L, int m0, int n0, int64
     for (int d = 0; d < kWD; ++d) {
       const int64_t b0 = c0 + d * kWK;
       const int buf = d & 1;
+      if (masked && b0 >= batch) return;
       if (masked) {
         a[d].mask(b0, batch);
         b[d].mask(b0, batch);
@@ -345,8 +347,10 @@ __device__ __forceinline__ void wgrad_tile(const WGrad& L, int m0, int n0, int64
           *reinterpret_cast<v4s*>(&Bs[buf][R::col() + k][R::row(g)]) = to_bf16x4(b[d].column(g, k));
         }
       __syncthreads();  // the other buffer was read before this barrier's arrival
-      a[d].load(L.A, L.lda, m0, b0 + kWD * kWK, batch);
-      b[d].load(L.dZ, L.ldz, n0, b0 + kWD * kWK, batch);
+      if (!masked) {
+        a[d].load(L.A, L.lda, m0, b0 + kWD * kWK, batch);
+        b[d].load(L.dZ, L.ldz, n0, b0 + kWD * kWK, batch);
+      }
       gemm_chunk<kWT, kWK, 1>(As[buf], Bs[buf], wm, wn, lane, acc);
     }
   };
