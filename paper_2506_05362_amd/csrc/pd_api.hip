@@ -104,6 +104,7 @@ struct pd_ctx {
   // follows when something else reads it
   uint32_t* lined = nullptr;
   uint64_t* lined_live = nullptr;
+  uint8_t* lined_news = nullptr;
   int16_t* offset_class = nullptr;
   bool lined_ahead = false;  // steps since colE followed
   bool lined_asked = false;  // made, or found not to be had, since the path was chosen
@@ -345,6 +346,7 @@ StepArgs step_args(pd_ctx* c) {
   A.lined_off = c->lined_off;
   A.lined_row = c->lined_row;
   A.lined_live = c->lined_live;
+  A.lined_news = c->lined_news;
   A.offset_class = c->offset_class;
   A.m = c->m;
   A.sentinel_hi = c->sentinel_hi;
@@ -967,6 +969,7 @@ AlignArgs align_args(pd_ctx* c) {
   a.lined = c->lined;
   a.row = c->lined_row;
   a.live = c->lined_live;
+  a.news = c->lined_news;
   a.sentinel_hi = c->sentinel_hi;
   a.axis_order = c->axis_order_d;
   a.axis_rank = c->axis_rank;
@@ -982,6 +985,7 @@ void drop_lined(pd_ctx* c) {
   dev_free(c, c->lined_off);
   dev_free(c, c->lined_row);
   dev_free(c, c->lined_live);
+  dev_free(c, c->lined_news);
   for (int b = 0; b < 2; ++b) {
     dev_free(c, c->uxy[b]);
     dev_free(c, c->uz[b]);
@@ -992,12 +996,14 @@ void drop_lined(pd_ctx* c) {
   c->lined_off = nullptr;
   c->lined_row = nullptr;
   c->lined_live = nullptr;
+  c->lined_news = nullptr;
   c->lined_ahead = false;
 }
 
 // what the lined rows and the split copy of u hold, from colE, colOrig and u4
 pd_status fill_lined(pd_ctx* c) {
   HIPCHK(c, launch_fill_i32(reinterpret_cast<int32_t*>(c->lined_live), 0, 2 * c->nslices * c->n_stencil, c->stream));
+  HIPCHK(c, launch_fill_i32(reinterpret_cast<int32_t*>(c->lined_news), 0, (c->nslices + 3) / 4, c->stream));
   HIPCHK(c, launch_align_fill(align_args(c), c->stream));
   for (int b = 0; b < 2; ++b) HIPCHK(c, launch_split_u(c->u4[b], c->uxy[b], c->uz[b], c->n, c->stream));
   c->lined_ahead = false;
@@ -1030,7 +1036,7 @@ pd_status make_lined(pd_ctx* c) {
     HIPCHK(c, hipMemcpyAsync(&words, c->lined_off + c->nslices, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     ok = words > 0 && get(&c->lined, words) && get(&c->lined_row, words / kWave) &&
-         get(&c->lined_live, c->nslices * c->n_stencil);
+         get(&c->lined_live, c->nslices * c->n_stencil) && get(&c->lined_news, 4 * ((c->nslices + 3) / 4));
     for (int b = 0; b < 2; ++b) ok = ok && get(&c->uxy[b], c->n) && get(&c->uz[b], c->n);
   }
   dev_free(c, scratch);

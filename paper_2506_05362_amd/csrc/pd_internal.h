@@ -171,6 +171,7 @@ struct StepArgs {
   const int64_t* lined_off;
   const int32_t* lined_row;
   uint64_t* lined_live;         // see AlignArgs
+  uint8_t* lined_news;
   const int16_t* offset_class;  // [(2 m + 1)^3] class of a lattice offset, -1 beyond the horizon
   int32_t m;
   int32_t* intact;
@@ -276,6 +277,7 @@ struct AlignArgs {
   uint32_t* lined;  // column words: node, with kBroken set where there is no bond (any more)
   int32_t* row;     // [off[nslices] / 64]
   uint64_t* live;   // [nslices][n_stencil] lanes whose bond of a class is intact
+  uint8_t* news;    // [nslices] a bond broke since the column words followed
   uint32_t sentinel_hi;
   int64_t n, nslices;
   const int32_t* axis_order;  // [G] axis order of the grain's node list

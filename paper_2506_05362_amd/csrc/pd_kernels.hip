@@ -320,19 +320,28 @@ __global__ __launch_bounds__(kBlock) void k_align(AlignArgs a) {
   }
 }
 
-// the column words of the slices with lined rows: an entry whose lane bit is clear becomes
-// a broken one
+// the column words of the slices in which a bond of the lined rows broke: an entry whose
+// lane bit is clear becomes a broken one
 __global__ void k_lined_to_cols(AlignArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   const int64_t s = i / kWave, lane = i % kWave;
-  if (a.off[s + 1] == a.off[s]) return;
-  for (int k = 0; k < a.rowlen[i]; ++k) {
+  if (!a.news[s]) return;
+  const int wide = (int)((a.slice_off[s + 1] - a.slice_off[s]) / kWave);
+  const uint64_t* live = a.live + s * a.n_stencil;
+  for (int k = 0; k < wide; k += kUnroll) {  // (padding has the class after the last)
     const int64_t at = a.slice_off[s] + (int64_t)k * kWave + lane;
-    const uint32_t wo = a.colOrig[at];
-    const bool intact = (a.live[s * a.n_stencil + (wo >> a.node_bits)] >> lane) & 1ull;
-    a.colE[at] = intact ? wo : (uint32_t)i | a.sentinel_hi;
+    uint32_t c[kUnroll];
+    uint64_t m[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) c[u] = a.colOrig[at + u * kWave] >> a.node_bits;
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) m[u] = live[c[u] < (uint32_t)a.n_stencil ? c[u] : 0u];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+      if (c[u] < (uint32_t)a.n_stencil && !((m[u] >> lane) & 1ull)) a.colE[at + u * kWave] = (uint32_t)i | a.sentinel_hi;
   }
+  a.news[s] = 0;  // (by every lane of the slice's wavefront, which has read it)
 }
 
 // ---------------------------------------------------------------------------
@@ -1197,9 +1206,11 @@ __device__ __forceinline__ void bonds_lined(const StepArgs& A, int64_t slice, in
         }
         // and in its class's mask, by atomics: lanes of another table share it
         const uint32_t k = (uint32_t)rc[u] / (uint32_t)sizeof(StencilC) % (uint32_t)(A.n_stencil + 1);
-        if (lane == 0)
+        if (lane == 0) {
           __hip_atomic_fetch_and(A.lined_live + slice * A.n_stencil + k, ~(live & ov & mine), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
+          A.lined_news[slice] = 1;
+        }
       }
     }
   };
