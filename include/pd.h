@@ -226,7 +226,13 @@ pd_status pd_build_bonds(pd_ctx* ctx, const pd_cut* cuts, int32_t n_cuts);
    length replay one captured HIP graph; the rest launch kernels directly.
    With PD_FLAG_ADAPTIVE_REBUILD the status is read after every such chunk
    (and every run of direct steps up to the next multiple), and an early
-   rebuild is not an error. */
+   rebuild is not an error.
+   On the sliced bond path, meshes of 262,144 nodes (4096 slices) and more step over a
+   second set of rows, in every loop but the persistent one.  The first call that needs
+   it, and the first after a change from the tiled path or the persistent loop, asks the
+   allocator for it (about 0.5 KB a node, all that pd_step ever allocates but for the
+   persistent loop's 8 bytes of barrier) and waits while it is filled.  Where the
+   memory is refused, the steps go on with the rows of the build: the same results. */
 pd_status pd_step(pd_ctx* ctx, int64_t n_steps);
 
 /* Bytes a field occupies (for sizing dst). */
@@ -234,6 +240,7 @@ pd_status pd_field_bytes(pd_ctx* ctx, pd_field field, int64_t* bytes);
 
 /* Copy a field into dst (host memory, or device memory when dst_on_device != 0).
    dst_bytes smaller than the field gives PD_ERR_INVALID.  Synchronises the stream.
+   Of the fields, only PD_FORCE_DENSITY and PD_ENERGY allocate (on their first call).
    Device memory is written on the context's stream: what other streams do with it
    has to be done by then. */
 pd_status pd_get(pd_ctx* ctx, pd_field field, void* dst, int64_t dst_bytes, int32_t dst_on_device);
@@ -300,8 +307,8 @@ pd_status pd_loop_counts(pd_ctx* ctx, int64_t* out6);
                          reduces the wall reactions;
      PD_LOOP_PER_GRAIN   unbatched reference: one launch per grain per step.
    slices_per_block: 64-node slices (wavefronts) per workgroup, 1, 2, 4 or 8
-   (GRAPH and DIRECT; the others use 4); fewer where that would leave compute
-   units without a workgroup.  xcd_remap: 1 maps consecutive
+   (GRAPH and DIRECT; the others use 4); in all but PERSISTENT fewer where a launch
+   would leave compute units without a workgroup.  xcd_remap: 1 maps consecutive
    workgroups to contiguous slice ranges per XCD, 0 keeps dispatch order.
    persistent_blocks: workgroups of the persistent launch, 0 = as many as can be
    resident.
@@ -321,7 +328,8 @@ pd_status pd_loop_counts(pd_ctx* ctx, int64_t* out6);
                       rounding, so with servo walls the node state does too.
    Switching the bond path hands the bond memory over; pd_get, pd_get_state
    and pd_set_state see the same bond state either way.  Setting a
-   configuration drops the captured graph. */
+   configuration drops the captured graph, and one with the tiled path or the
+   persistent loop gives back the second set of rows (see pd_step). */
 enum { PD_LOOP_GRAPH = 0, PD_LOOP_DIRECT = 1, PD_LOOP_PERSISTENT = 2, PD_LOOP_PER_GRAIN = 3 };
 enum { PD_BONDS_SLICES = 0, PD_BONDS_TILES = 1 };
 typedef struct {

@@ -811,6 +811,7 @@ pd_status pdm_create(pdm_net** out, const int32_t* dims, int32_t n_dims, int64_t
   TRY(alloc(n, &n->yhat, max_batch * dims[L]));
   TRY(alloc(n, &n->xrows, max_batch * row4(dims[0])));
   if (n_dims == 5 && dims[1] == kH && dims[2] == kH && dims[3] == kH && dims[0] <= 16 && dims[4] <= 16) {
+    // (the LDS of gfx950; the kernel's 77 KB are more than other devices give a workgroup)
     int dev = 0, lds = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&

@@ -646,16 +646,6 @@ bool any_servo(const pd_ctx* c) {
 // The six axis orders (slowest first), as in the tile kernels.
 constexpr int kAxisOrders[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
 
-// Tiles of the bond loop: for every grain an axis order in which its node
-// indices ascend lexicographically (the order of the slice path's sorted rows),
-// its box on those axes, a cell -> node map, the 8 x 4 x 16-cell tiles that hold
-// nodes, the bond table of each (stencil class, axis order) in tile class order
-// and the class masks of the built bonds.  When every grain shares one
-// lattice (equal spacing, origins a whole number of spacings apart), one bond
-// table and one axis order, the tiles cover one box over all grains instead
-// (lattice mode): a dense aggregate then fills its tiles, and bonds, which
-// never join two grains, are told apart by the class masks.  Leaves tile_ok = 0
-// when some grain has no such order or the horizon factor is not 3.
 // the axis order in which a grain lists its nodes lexicographically, -1 if in none
 int lattice_order(const pd_ctx* c, int32_t g) {
   const int64_t N = c->n, b = c->grain_begin[(size_t)g], e = c->grain_begin[(size_t)g + 1];
@@ -713,6 +703,16 @@ pd_status rank_classes(pd_ctx* c, const std::vector<int32_t>& stencil) {
   return PD_OK;
 }
 
+// Tiles of the bond loop: for every grain an axis order in which its node
+// indices ascend lexicographically (the order of the slice path's sorted rows),
+// its box on those axes, a cell -> node map, the 8 x 4 x 16-cell tiles that hold
+// nodes, the bond table of each (stencil class, axis order) in tile class order
+// and the class masks of the built bonds.  When every grain shares one
+// lattice (equal spacing, origins a whole number of spacings apart), one bond
+// table and one axis order, the tiles cover one box over all grains instead
+// (lattice mode): a dense aggregate then fills its tiles, and bonds, which
+// never join two grains, are told apart by the class masks.  Leaves tile_ok = 0
+// when some grain has no such order or the horizon factor is not 3.
 pd_status build_tiles(pd_ctx* c) {
   c->tile_ok = 0;
   c->tile_lattice = 0;

@@ -1260,9 +1260,9 @@ __device__ __forceinline__ void stage_stencil(const StepArgs& A, StencilC* s_st)
   __syncthreads();
 }
 
-// DEPTH 2 in 128 registers, so that four wavefronts a SIMD stay resident; DEPTH 4
-// for meshes that leave a SIMD two wavefronts or fewer, whose only cover for a
-// gather is their own other gathers.
+// DEPTH 2 in 128 registers, so that four wavefronts a SIMD stay resident; DEPTH 4, at
+// two, for meshes that leave a SIMD one wavefront or less, whose only cover for a
+// gather is its own other gathers.
 template <int MODE, bool ABS, int SPB, int DEPTH, bool LINED>
 __global__ __launch_bounds__(SPB * kWave) __attribute__((amdgpu_waves_per_eu(DEPTH > 2 ? 2 : PD_STEP_WAVES_PER_EU)))
 void k_step(StepArgs A) {
@@ -1591,8 +1591,11 @@ __global__ __launch_bounds__(kTS * kWave) __attribute__((amdgpu_waves_per_eu(4))
   // box) has no bonds: its wavefront leaves the vector units to the others
   if (__ballot(valid) != 0ull) {
     const auto classes = std::make_integer_sequence<int, kTileClasses>{};
-    // the two node orders of the meshes that fill tiles best (x-y-z of a shared
-    // lattice, x-z-y of a plate) have the zero components of xi compiled out
+    // the node orders of a shared lattice (x-y-z) and of a plate thin along z (x-z-y) have
+    // the zero components of xi compiled out: a slab of 200 x 20 x 192 nodes takes 102 to
+    // 107 us a step in these two orders, 108 to 112 in the four others, all of which took
+    // 126 to 130 before (a variant for each order, with and without the |s| reading, would
+    // be six times the code)
     if (!ABS && TG.perm == 0)
       tile_bonds<ABS, 0>(classes, L, Lz, tab, norms, mrow_r, mrow_w, ui.x, ui.y, ui.z, nbroke, fx, fy, fz);
     else if (!ABS && TG.perm == 1)
@@ -1893,7 +1896,7 @@ __device__ __forceinline__ void grid_release(const BarrierArgs& B) {
 }
 
 template <bool ABS>
-__global__ __launch_bounds__(4 * kWave) __attribute__((amdgpu_waves_per_eu(kUnroll > 4 ? 3 : 4)))
+__global__ __launch_bounds__(4 * kWave) __attribute__((amdgpu_waves_per_eu(3)))
 void k_step_persistent(StepArgs A, int64_t nsteps, BarrierArgs B) {
   extern __shared__ StencilC s_st[];
   __shared__ double red[kMaxWalls * 3][1024 / kWave];
@@ -2832,7 +2835,9 @@ static void launch_step_t(const StepArgs& a, hipStream_t s, hipEvent_t e0 = null
   const bool deep = a.slice_end - a.slice_base <= kDeepSlices;
   if constexpr (MODE == MODE_STEP) {
     if (a.lined) return launch_step_d<MODE, SPB, 2, true>(a, s, e0, e1);
-    if (deep) return launch_step_d<MODE, SPB, 4, false>(a, s, e0, e1);
+    // (so few slices never run eight to a workgroup, see launch_step_spb)
+    if constexpr (SPB < 8)
+      if (deep) return launch_step_d<MODE, SPB, 4, false>(a, s, e0, e1);
   }
   launch_step_d<MODE, SPB, 2, false>(a, s, e0, e1);
 }
