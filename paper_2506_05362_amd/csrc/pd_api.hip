@@ -1045,7 +1045,13 @@ pd_status make_lined(pd_ctx* c) {
     drop_lined(c);
     return PD_OK;
   }
-  return fill_lined(c);
+  const pd_status st = fill_lined(c);
+  if (st != PD_OK) {  // (half-filled rows are not stepped over)
+    (void)hipStreamSynchronize(c->stream);
+    drop_lined(c);
+    c->lined_asked = false;
+  }
+  return st;
 }
 
 // the tile path keeps the bond memory in class masks, lined rows in their own words;
