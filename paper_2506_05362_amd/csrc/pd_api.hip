@@ -127,7 +127,8 @@ struct pd_ctx {
   int64_t* grid = nullptr;  // [8] cell grid of the last rebuild
   double* u_build = nullptr;
   long long* gbox = nullptr;
-  int32_t* isolated = nullptr;
+  int32_t* binned = nullptr;
+  double* nearbox = nullptr;
   int64_t* scan64 = nullptr;
   double* energy_partial = nullptr;
   double* scratch_dev = nullptr;  // this context's GPU's copy of the allocation-free scratch
@@ -419,7 +420,8 @@ ContactArgs contact_args(pd_ctx* c, int buf) {
   C.cand = c->cand;
   C.u_build = c->u_build;
   C.gbox = c->gbox;
-  C.isolated = c->isolated;
+  C.binned = c->binned;
+  C.nearbox = c->nearbox;
   C.box_chunks = c->box_chunks;
   C.n_box_chunks = c->n_box_chunks;
   C.n_grains = c->n_grains;
@@ -1536,7 +1538,8 @@ pd_status pd_build_bonds(pd_ctx* c, const pd_cut* cuts, int32_t n_cuts) {
   TRY(alloc_n(c, &c->cand, c->capacity, "candidates"));
   TRY(alloc_n(c, &c->u_build, 3 * N, "positions at rebuild"));
   TRY(alloc_n(c, &c->gbox, 6 * (int64_t)G, "grain boxes"));
-  TRY(alloc_n(c, &c->isolated, G, "isolated grains"));
+  TRY(alloc_n(c, &c->binned, G, "grains to bin"));
+  TRY(alloc_n(c, &c->nearbox, 6 * (int64_t)G, "boxes near grains"));
   TRY(alloc_n(c, &c->grain_begin_d, (int64_t)G + 1, "grain node ranges"));
   {
     const std::vector<int32_t> gb(c->grain_begin.begin(), c->grain_begin.end());

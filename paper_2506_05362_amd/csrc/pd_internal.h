@@ -316,7 +316,8 @@ struct ContactArgs {
   double* u_build;        // SoA
   long long* gbox;        // [G][6] order-preserving encodings of min xyz, max xyz of p
   const int32_t* grain_begin;  // [G+1] first node of each grain
-  int32_t* isolated;      // [G] no other grain's box within the cutoff: not binned, no candidates
+  int32_t* binned;        // [G] which of a grain's nodes are (k_near_boxes); the others have no candidates
+  double* nearbox;        // [G][6] min xyz, max xyz around the boxes near a grain, wider by the cutoff
   const int64_t* box_chunks;  // [n_box_chunks][3]: grain, first node, end node (one grain each)
   int32_t n_box_chunks;
   int32_t n_grains;
