@@ -10,7 +10,8 @@ from paper_2506_05362_amd import inputs as I
 from test_gpu_device_memory import Recorder
 
 pytestmark = pytest.mark.gpu
-FIELDS = ("displacement", "velocity", "accel", "intact_count", "bond_broken", "force_density", "energy", "damage")
+# (energies first: the first field that brings the column words up to date)
+FIELDS = ("energy", "displacement", "velocity", "accel", "intact_count", "bond_broken", "force_density", "damage")
 
 
 @pytest.fixture(scope="module")
@@ -45,7 +46,6 @@ def _equal(sims, what):
     for sim in sims[1:]:
         for f in FIELDS:
             got = sim.get(f)
-            # the energies are sums over workgroups, taken in the same order
             assert np.array_equal(got, want[f]), (what, f)
     return want
 
